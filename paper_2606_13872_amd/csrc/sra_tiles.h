@@ -18,6 +18,10 @@ namespace sra {
 // use D + 32, and tiles read both ways use D + 24 or D + 8 with permuted rows (below).
 template <int D> constexpr int kRowPadRS = D + 8;
 template <int D> constexpr int kTrPadRS = D + 32;
+// The operands of 16x16x32 MFMAs read rows of 16 (row fragments: 16 rows x 64 bytes; transpose
+// reads: 8 rows x 32 bytes served together): plain rows at D + 16 serve both without conflicts
+// (4.5 and 2.6 cycles per wave read; at D + 8: 8.2 and 4.3).
+template <int D> constexpr int kPadRS = D + 16;
 template <int D> constexpr int kBothPadRS = D + 24;
 // Tiles read both as row fragments and through the transpose read are stored at the
 // row-fragment stride (D + 8) with their rows permuted inside each block of 16: logical row
@@ -82,6 +86,109 @@ __device__ __forceinline__ void lds_dma_x4_at(const void* g, uint32_t la) {
       : "memory");
 }
 
+// The same with a uniform global base and a 32-bit byte offset per lane.
+__device__ __forceinline__ void lds_dma_x4_off(uint64_t base, uint32_t off, uint32_t la) {
+  uint32_t saved;
+  asm volatile(
+      "s_mov_b32 %0, m0\n\t"
+      "s_mov_b32 m0, %3\n\t"
+      "s_nop 0\n\t"
+      "global_load_lds_dwordx4 %1, %2\n\t"
+      "s_mov_b32 m0, %0"
+      : "=&s"(saved)
+      : "v"(off), "s"(base), "s"(la)
+      : "memory");
+}
+
+// Swizzled LDS tiles: NR rows of D bf16 without padding, the 16-byte chunks of row r XORed with
+// swz<D>(r). Both reads of the 16x16x32 MFMA operands are then free of bank conflicts (row
+// fragments by ds_read_b128, whose lanes {0-3, 12-15, 20-27} are served together, and transpose
+// reads, served 32 lanes at a time: 4.5 and 2.6 cycles per wave read measured, against 8.1 and
+// 4.3 with two-way conflicts), and a tile is a whole number of 1 KB loads.
+template <int D>
+__host__ __device__ constexpr int swz(int r) {
+  return D == 128 ? 2 * (r & 7) : 2 * ((r >> 1) & 3);
+}
+template <int D, int NR>
+struct SwzTile {
+  static constexpr int kInstr = NR * D / 512;    // 1 KB load instructions
+  static constexpr int kElems = NR * D;
+  static constexpr int kRowsPerInstr = 512 / D;
+};
+// Byte address of this lane's part of row fragment c = 0 (rows 0..15, head dims 0..31); fragment c
+// is at the address XOR 64 c, rows 16 n further at + 32 n D.
+template <int D>
+__device__ __forceinline__ uint32_t swz_row_addr() {
+  const int lane = threadIdx.x & 63, r = lane & 15;
+  return uint32_t(r * D * 2 + (((lane >> 4) ^ swz<D>(r)) * 16));
+}
+// The same for the transpose reads of a 16-row x 16-dim block (lane group g holds rows 4 g .. + 3):
+// head dims 16 db .. + 15 are at the address XOR 32 db.
+template <int D>
+__device__ __forceinline__ uint32_t swz_tr_addr() {
+  const int lane = threadIdx.x & 63, r = 4 * (lane >> 4) + ((lane & 15) >> 2);
+  return uint32_t(r * D * 2 + ((((lane & 3) >> 1) ^ swz<D>(r)) * 16) + (lane & 1) * 8);
+}
+// a XOR a constant, computed where it stands: left to the compiler, the addresses of a phase's
+// fragments are all computed ahead of it and hold a register each.
+template <int K>
+__device__ __forceinline__ uint32_t xor_here(uint32_t a) {
+  if constexpr (K == 0) return a;
+  uint32_t r;
+  asm volatile("v_xor_b32 %0, %2, %1" : "=v"(r) : "v"(a), "i"(K));
+  return r;
+}
+__device__ __forceinline__ bf16x8 lds_ld8(uint32_t a) {
+  return *(const __attribute__((address_space(3))) bf16x8*)(uintptr_t)a;
+}
+__device__ __forceinline__ floatx4 lds_ld4f(uint32_t a) {
+  return *(const __attribute__((address_space(3))) floatx4*)(uintptr_t)a;
+}
+__device__ __forceinline__ void lds_st_f(uint32_t a, float x) {
+  *(__attribute__((address_space(3))) float*)(uintptr_t)a = x;
+}
+__device__ __forceinline__ bf16x4 lds_ld_tr(uint32_t a) {
+  return __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(uintptr_t)a);
+}
+// Byte offset of this lane's chunk of load instruction `wave` of a swizzled tile from the tile's
+// first row (the instructions of a wave are a multiple of 4 apart, so they share it up to a
+// whole number of rows).
+template <int D>
+__device__ __forceinline__ uint32_t swz_load_off(int64_t stride, int head, int wave) {
+  constexpr int CPR = D / 8;
+  const int lane = threadIdx.x & 63, r = wave * (512 / D) + lane / CPR;
+  return uint32_t((int64_t(r) * stride + head * D + ((lane % CPR) ^ swz<D>(r)) * 8) * 2);
+}
+// Rows [off, off + NR) of a span into a swizzled tile, rows past the span's end clamped to its last.
+template <int D, int NR, int NW>
+__device__ __forceinline__ void swz_load_clamped(uint32_t la, uint64_t src, int64_t stride, int head, int start, int len,
+                                                 int off, int wave) {
+  constexpr int CPR = D / 8, RPI = 512 / D;
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int j = 0; j < SwzTile<D, NR>::kInstr / NW; ++j) {
+    const int r = (wave + j * NW) * RPI + lane / CPR;
+    const int rr = min(off + r, len - 1);
+    const __bf16* g = reinterpret_cast<const __bf16*>(src) + int64_t(start + rr) * stride + head * D +
+                      ((lane % CPR) ^ swz<D>(r)) * 8;
+    lds_dma_x4_at(g, la + (wave + j * NW) * 1024);
+  }
+}
+
+// The same for 4 bytes per lane (lane l's land at la + 4 l).
+__device__ __forceinline__ void lds_dma_x1_off(uint64_t base, uint32_t off, uint32_t la) {
+  uint32_t saved;
+  asm volatile(
+      "s_mov_b32 %0, m0\n\t"
+      "s_mov_b32 m0, %3\n\t"
+      "s_nop 0\n\t"
+      "global_load_lds_dword %1, %2\n\t"
+      "s_mov_b32 m0, %0"
+      : "=&s"(saved)
+      : "v"(off), "s"(base), "s"(la)
+      : "memory");
+}
+
 // Direct global -> LDS copy (gfx950 GLOBAL_LOAD_LDS_DWORDX4) of rows [off, off + NR) of a span
 // into a padded tile. Each wave instruction fills 1 KB of LDS: lane l writes the 16 bytes at
 // (LDS base + 16 l), so lane l fetches the global chunk that belongs there; lanes that land on
@@ -143,6 +250,14 @@ struct TileLoader {
 
 __device__ __forceinline__ void wait_vmem() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
+// A workgroup barrier that waits for nothing else: LDS reads and direct loads in flight stay so
+// (__syncthreads waits for all of them). The caller has waited for the loads that are read next.
+__device__ __forceinline__ void block_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
 // Walks the flattened sequence of NR-row steps over a work item's span list, keeping the
 // current span's fields in registers (the span table is read once per span).
 struct SpanCursor {
@@ -174,6 +289,39 @@ struct SpanCursor {
       ++si;
       off = 0;
       load();
+    }
+  }
+};
+
+// Walks the full STEP-row tiles of a span list (ragged span ends are skipped).
+template <int STEP>
+struct FullTileCursor {
+  const Span* spans;
+  int n, si, off, cur_stream, cur_start, cur_len;
+  __device__ __forceinline__ void settle() {
+    while (si < n) {
+      const Span s = spans[si];
+      cur_stream = __builtin_amdgcn_readfirstlane(s.stream);
+      cur_start = __builtin_amdgcn_readfirstlane(s.start);
+      cur_len = __builtin_amdgcn_readfirstlane(s.len);
+      if (off + STEP <= cur_len) return;
+      ++si;
+      off = 0;
+    }
+  }
+  __device__ __forceinline__ void init(const Span* s, int count) {
+    spans = s;
+    n = count;
+    si = 0;
+    off = 0;
+    settle();
+  }
+  __device__ __forceinline__ void advance() {
+    off += STEP;
+    if (off + STEP > cur_len) {
+      ++si;
+      off = 0;
+      settle();
     }
   }
 };
