@@ -6,30 +6,12 @@
 namespace sra {
 
 // Padded LDS tiles: NR rows of D bf16 with a row stride of RS elements, so every fragment
-// address is one per-lane base plus a compile-time offset. The stride decides the bank
-// pattern; measured on gfx950 (LDS read bytes per clock per CU, 16-byte aligned strides):
-//   row stride (D = 128)   row fragment (ds_read_b128)   transpose read (ds_read_b64_tr_b16)
-//   256 B                   16                            64
-//   272 B  (D + 8)         128                            64
-//   288 B  (D + 16)         64                           122
-//   304 B  (D + 24)        128                           122
-//   320 B  (D + 32)         32                           203
-// so tiles read only as row fragments use D + 8, tiles read only through the transpose read
-// use D + 32, and tiles read both ways use D + 24 or D + 8 with permuted rows (below).
-template <int D> constexpr int kRowPadRS = D + 8;
-template <int D> constexpr int kTrPadRS = D + 32;
-// The operands of 16x16x32 MFMAs read rows of 16 (row fragments: 16 rows x 64 bytes; transpose
-// reads: 8 rows x 32 bytes served together): plain rows at D + 16 serve both without conflicts
-// (4.5 and 2.6 cycles per wave read; at D + 8: 8.2 and 4.3).
+// address is one per-lane base plus a compile-time offset. The operands of 16x16x32 MFMAs read
+// rows of 16 (row fragments by ds_read_b128: 16 rows x 64 bytes, lanes {0-3, 12-15, 20-27} and
+// so on served together; transpose reads by ds_read_b64_tr_b16: 8 rows x 32 bytes served
+// together): a stride of D + 16 serves both without bank conflicts (measured 4.5 and 2.6 cycles
+// per wave read; D + 8 takes 8.2 and 4.3, D + 24 8.2 and 4.3).
 template <int D> constexpr int kPadRS = D + 16;
-template <int D> constexpr int kBothPadRS = D + 24;
-// Tiles read both as row fragments and through the transpose read are stored at the
-// row-fragment stride (D + 8) with their rows permuted inside each block of 16: logical row
-// r = 4a + b (a, b < 4) sits at physical row 4b + a. A row fragment (16 consecutive rows, one
-// 16-byte chunk each) still meets 16 distinct bank groups, and so does a transpose read
-// (4 consecutive rows, 4 chunks each), which the plain D + 8 stride does not give. The map is
-// its own inverse, and for r < 8 it sends r + 8 to perm16(r) + 2.
-__host__ __device__ constexpr int perm16(int r) { return (r & ~15) | ((r & 3) << 2) | ((r >> 2) & 3); }
 
 template <int D, int NR, int RS>
 struct PaddedTile {
@@ -194,11 +176,10 @@ __device__ __forceinline__ void lds_dma_x1_off(uint64_t base, uint32_t off, uint
 // (LDS base + 16 l), so lane l fetches the global chunk that belongs there; lanes that land on
 // a pad slot fetch an in-bounds chunk that nothing reads. Rows past the span end are clamped
 // to its last row (the kernels mask them). Instructions are dealt over the NW waves.
-template <int D, int NR, int RS, int NW, bool kPerm = false>
+template <int D, int NR, int RS, int NW>
 __device__ __forceinline__ void tile_load_lds(__bf16* lds, const __bf16* __restrict__ src, int64_t stride,
                                               int head, int start, int len, int off, int wave) {
   using TL = PaddedTile<D, NR, RS>;
-  static_assert(!kPerm || NR % 16 == 0, "permuted tiles hold whole 16-row blocks");
   constexpr int SPR = TL::kSlotsPerRow, CPR = D / 8;
   const int lane = threadIdx.x & 63;
 #pragma unroll
@@ -206,8 +187,7 @@ __device__ __forceinline__ void tile_load_lds(__bf16* lds, const __bf16* __restr
     const int ins = wave + j * NW;
     if (ins < TL::kInstr) {
       const int p = ins * 64 + lane;
-      const int prow = min(p / SPR, NR - 1);
-      const int row = kPerm ? perm16(prow) : prow;  // logical row stored at physical row prow
+      const int row = min(p / SPR, NR - 1);
       const int slot = p % SPR;
       const int ch = slot < CPR ? slot : 0;
       const int rr = min(off + row, len - 1);
@@ -219,10 +199,9 @@ __device__ __forceinline__ void tile_load_lds(__bf16* lds, const __bf16* __restr
 
 // Per-lane address offsets of the direct loads of a padded tile, for tiles whose NR rows all
 // lie inside the span (no clamping): lane offsets are fixed, only the tile's first row moves.
-template <int D, int NR, int RS, int NW, bool kPerm = false>
+template <int D, int NR, int RS, int NW>
 struct TileLoader {
   using TL = PaddedTile<D, NR, RS>;
-  static_assert(!kPerm || NR % 16 == 0, "permuted tiles hold whole 16-row blocks");
   static constexpr int kSlots = (TL::kInstr + NW - 1) / NW;
   int voff[kSlots];  // element offset of this lane's chunk from the tile's first row
   __device__ __forceinline__ void init(int64_t stride, int head, int wave) {
@@ -231,19 +210,9 @@ struct TileLoader {
 #pragma unroll
     for (int j = 0; j < kSlots; ++j) {
       const int p = (wave + j * NW) * 64 + lane;
-      const int prow = min(p / SPR, NR - 1);
-      const int row = kPerm ? perm16(prow) : prow;
+      const int row = min(p / SPR, NR - 1);
       const int slot = p % SPR;
       voff[j] = int(row * stride) + head * D + (slot < CPR ? slot : 0) * 8;
-    }
-  }
-  // `first_row` points at the tile's first row (uniform); every row is inside the span.
-  __device__ __forceinline__ void issue(__bf16* lds, const __bf16* first_row, int wave) const {
-#pragma unroll
-    for (int j = 0; j < kSlots; ++j) {
-      const int ins = wave + j * NW;
-      if (ins < TL::kInstr)
-        lds_dma_x4(first_row + voff[j], lds + ins * 512);
     }
   }
 };
@@ -257,41 +226,6 @@ __device__ __forceinline__ void block_barrier() {
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
 }
-
-// Walks the flattened sequence of NR-row steps over a work item's span list, keeping the
-// current span's fields in registers (the span table is read once per span).
-struct SpanCursor {
-  const Span* spans;
-  int n, si, off;
-  int cur_stream, cur_start, cur_len;
-  __device__ __forceinline__ void load() {
-    if (si < n) {
-      const Span s = spans[si];
-      cur_stream = __builtin_amdgcn_readfirstlane(s.stream);
-      cur_start = __builtin_amdgcn_readfirstlane(s.start);
-      cur_len = __builtin_amdgcn_readfirstlane(s.len);
-    }
-  }
-  __device__ __forceinline__ void init(const Span* s, int count) {
-    spans = s;
-    n = count;
-    si = 0;
-    off = 0;
-    load();
-  }
-  __device__ __forceinline__ bool valid() const { return si < n; }
-  __device__ __forceinline__ int stream() const { return cur_stream; }
-  __device__ __forceinline__ int start() const { return cur_start; }
-  __device__ __forceinline__ int len() const { return cur_len; }
-  __device__ __forceinline__ void advance(int step) {
-    off += step;
-    if (off >= cur_len) {
-      ++si;
-      off = 0;
-      load();
-    }
-  }
-};
 
 // Walks the full STEP-row tiles of a span list (ragged span ends are skipped).
 template <int STEP>
@@ -325,11 +259,5 @@ struct FullTileCursor {
     }
   }
 };
-
-__device__ __forceinline__ int count_steps(const Span* s, int n, int step) {
-  int t = 0;
-  for (int i = 0; i < n; ++i) t += (s[i].len + step - 1) / step;
-  return t;
-}
 
 }  // namespace sra
