@@ -204,6 +204,19 @@ sra_status sra_schedule_info(const sra_problem* p, int which, int64_t* n_items,
  * visibility mask. out must hold (G+R)^2 bytes (host). */
 sra_status sra_schedule_mask(const sra_problem* p, int which, int32_t sample, uint8_t* out);
 
+/* What a call launches for schedule `which`. The hooks above report whole work items of 256 rows;
+ * a call may take larger tiles, and splits items along their spans (their partial results are
+ * combined by a kernel of their own) where too few, too long items would leave compute units
+ * idle. n_items: work items and pieces, tile: rows per work item, split_items: items that are
+ * split; any may be NULL. Host only. */
+sra_status sra_launch_info(const sra_problem* p, int which, int64_t* n_items, int64_t* tile,
+                           int64_t* split_items);
+
+/* sra_schedule_mask of what a call launches, for head `head`: the pieces of a split item cover
+ * its pairs once between them, so the matrix is again exactly the 0/1 visibility mask. */
+sra_status sra_launch_mask(const sra_problem* p, int which, int32_t sample, int32_t head,
+                           uint8_t* out);
+
 /* Copies schedule `which` (the tiles realising §1, §2.1 and §4.3) into host buffers:
  * items[8*i + 0..7] = {stream, head, start, length,
  * span_offset, span_count, sample, reserved} per work item, spans[4*j + 0..3] = {stream,
@@ -211,7 +224,7 @@ sra_status sra_schedule_mask(const sra_problem* p, int which, int32_t sample, ui
  * the dK/dV schedule only: the item's keys [lo, hi), counted from its first key, that the
  * span's queries see, packed lo | hi << 16, or 0 for all of them).
  * items/spans may be NULL to query only; capacities count int32 elements.
- * Items are listed in launch order (item i runs on XCD i % 8). When the head count is a
+ * Items are whole (256 rows) and listed in launch order (item i runs on XCD i % 8). When the head count is a
  * multiple of 8, an item whose first span is its sample's gen rows may start that span part
  * way in and wrap around (the span then appears as two entries, its tail first), so that the
  * items resident on one XCD stream the same rows at the same time; the rows covered are the

@@ -215,7 +215,7 @@ void emit_items(const TileClass& c, int tile, int32_t heads, int step,
       w.span_off = c.span_off;
       w.span_cnt = c.span_cnt;
       w.sample = c.sample;
-      w.reserved = 0;
+      w.slot = 0;
       out->push_back({int64_t(tile) * step_rows, w});
     }
 }
@@ -302,8 +302,10 @@ void align_phases(int step, Schedule* s) {
   s->spans.swap(spans);
 }
 
-// Query-major schedule (forward and dQ): query tiles of `tile` rows, key spans per class.
-void build_query_major(const Layout& L, int tile, int step, Schedule* s) {
+typedef std::vector<std::pair<int64_t, WorkItem>> CostedItems;
+
+// Query-major items (forward and dQ): query tiles of `tile` rows, key spans per class.
+CostedItems query_major_items(const Layout& L, int tile, int step, Schedule* s) {
   std::vector<TileClass> classes;
   s->spans.clear();
   for (int32_t b = 0; b < L.batch; ++b) {
@@ -340,10 +342,9 @@ void build_query_major(const Layout& L, int tile, int step, Schedule* s) {
         classes.push_back({1, sm.ref_off + r.r0, r.r1 - r.r0, off, int32_t(runs.size()), b, 0});
     }
   }
-  std::vector<std::pair<int64_t, WorkItem>> v;
+  CostedItems v;
   for (const TileClass& c : classes) emit_items(c, tile, L.heads, step, s->spans, &v);
-  order_items(v, L.heads, false, s);
-  if (L.heads % kNumXcd == 0) align_phases(step, s);
+  return v;
 }
 
 // First frame of the ref group holding sample-relative ref row r.
@@ -355,10 +356,10 @@ int32_t group_of_row(const SampleLayout& s, int64_t r) {
   return int32_t(r / s.F) / s.group * s.group;
 }
 
-// Key-major schedule (dK/dV): key tiles, query spans per class.
-void build_key_major(const Layout& L, int tile, int step, Schedule* s) {
+// Key-major items (dK/dV): key tiles, query spans per class.
+CostedItems key_major_items(const Layout& L, int tile, int step, Schedule* s) {
   std::vector<TileClass> classes;
-  std::vector<std::pair<int64_t, WorkItem>> v;
+  CostedItems v;
   s->spans.clear();
   std::map<std::vector<int32_t>, int32_t> lists;  // span list (flattened) -> offset
   auto intern = [&](const std::vector<Span>& l) {
@@ -419,15 +420,189 @@ void build_key_major(const Layout& L, int tile, int step, Schedule* s) {
           w.span_off = off;
           w.span_cnt = int32_t(l.size());
           w.sample = b;
-          w.reserved = 0;
+          w.slot = 0;
           v.push_back({int64_t(tile) * step_rows, w});
         }
       }
     }
   }
   for (const TileClass& c : classes) emit_items(c, tile, L.heads, step, s->spans, &v);
-  order_items(v, L.heads, true, s);
+  return v;
+}
+
+// A schedule of whole items in launch order.
+void finish_whole(CostedItems& v, const Layout& L, int step, bool heads_in_turn, Schedule* s) {
+  order_items(v, L.heads, heads_in_turn, s);
   if (L.heads % kNumXcd == 0) align_phases(step, s);
+}
+
+// ---- splitting
+
+// Times of a kernel in units of one 64-row step of a 256-row work item.
+struct KernelCost {
+  double step;     // one step
+  double item;     // prologue and epilogue of a work item
+  double piece;    // more of that for a piece, whose fp32 sums are written and read again
+  double combine;  // the combine launch
+};
+
+// When a launch of these times, longest first, would end on kNumCus compute units.
+double makespan(std::vector<double>& t) {
+  std::sort(t.begin(), t.end(), std::greater<double>());
+  std::priority_queue<double, std::vector<double>, std::greater<double>> cu;
+  double end = 0;
+  for (double x : t) {
+    double at = 0;
+    if (int(cu.size()) >= kNumCus) {
+      at = cu.top();
+      cu.pop();
+    }
+    cu.push(at + x);
+    end = std::max(end, at + x);
+  }
+  return end;
+}
+
+int32_t span_steps(const Span& x) { return (x.len + kStep - 1) / kStep; }
+
+// Pieces per item (same order as `steps`, which is longest first) that end the launch earliest, or
+// all ones; *end is that time. Tried: every item longer than a part of the longest cut to such
+// parts, and the same for only those items of the long ones that a last, partial round of the
+// compute units would hold. Launches of over 16 rounds lose less than their last round is worth.
+std::vector<int32_t> choose_split(const std::vector<int32_t>& steps, const KernelCost& c, int64_t max_slots,
+                                  double* end) {
+  const size_t n = steps.size();
+  std::vector<int32_t> best(n, 1), k(n);
+  if (n == 0) return *end = 0, best;
+  double total = 0;
+  for (int32_t x : steps) total += x * c.step + c.item;
+  if (n > size_t(16 * kNumCus)) {
+    *end = total / kNumCus + 0.5 * (steps[0] * c.step + c.item);
+    return best;
+  }
+  std::vector<double> t;
+  auto eval = [&](const std::vector<int32_t>& parts) {
+    t.clear();
+    bool any = false;
+    for (size_t i = 0; i < n; ++i) {
+      any |= parts[i] > 1;
+      for (int32_t j = 0; j < parts[i]; ++j)
+        t.push_back(double(steps[i]) / parts[i] * c.step + c.item + (parts[i] > 1 ? c.piece : 0));
+    }
+    return makespan(t) + (any ? c.combine : 0);
+  };
+  *end = eval(best);
+  const double whole = *end;
+  size_t n_long = 0;
+  while (n_long < n && 2 * steps[n_long] >= steps[0]) ++n_long;
+  const size_t rounds = n_long / kNumCus * kNumCus;
+  for (int32_t parts = 2; parts <= 24; ++parts) {
+    const int32_t piece = std::max<int32_t>(2, (steps[0] + parts - 1) / parts);
+    for (int tail = 0; tail < (rounds > 0 ? 2 : 1); ++tail) {
+      const size_t first = tail ? rounds : 0;
+      int64_t slots = 0;
+      for (size_t i = 0; i < n; ++i) {
+        k[i] = i < first ? 1 : std::max<int32_t>(1, (steps[i] + piece - 1) / piece);
+        if (k[i] > 1) slots += k[i];
+      }
+      if (slots == 0 || slots > max_slots) continue;
+      const double e = eval(k);
+      if (e < *end && e < 0.97 * whole) {
+        *end = e;
+        best = k;
+      }
+    }
+  }
+  return best;
+}
+
+// Replaces the items of v (longest first, with their spans in s) by their pieces, into s.
+void split_items(const CostedItems& v, const std::vector<int32_t>& parts, Schedule* s) {
+  std::vector<Span> spans;
+  std::map<std::pair<int32_t, std::pair<int32_t, int32_t>>, std::pair<int32_t, int32_t>> made;
+  std::vector<std::pair<int32_t, WorkItem>> out;
+  // steps [s0, s1) of a span list as a list of its own: its offset and length
+  auto cut = [&](const WorkItem& w, int32_t s0, int32_t s1) {
+    const auto key = std::make_pair(w.span_off, std::make_pair(s0, s1));
+    const auto it = made.find(key);
+    if (it != made.end()) return it->second;
+    const int32_t off = int32_t(spans.size());
+    int32_t at = 0;
+    for (int32_t i = 0; i < w.span_cnt && at < s1; ++i) {
+      const Span& x = s->spans[size_t(w.span_off) + i];
+      const int32_t m = span_steps(x), a = std::max(s0, at) - at, b = std::min(s1, at + m) - at;
+      if (a < b) spans.push_back({x.stream, x.start + a * kStep, std::min(x.len, b * kStep) - a * kStep, x.keys});
+      at += m;
+    }
+    return made[key] = {off, int32_t(spans.size()) - off};
+  };
+  for (size_t i = 0; i < v.size(); ++i) {
+    WorkItem w = v[i].second;
+    int32_t n = 0;
+    for (int32_t j = 0; j < w.span_cnt; ++j) n += span_steps(s->spans[size_t(w.span_off) + j]);
+    if (parts[i] > 1) {
+      s->combine.push_back({w.stream, w.head, w.start, w.len, s->slots, parts[i], {0, 0}});
+    }
+    for (int32_t j = 0; j < parts[i]; ++j) {
+      const int32_t s0 = int32_t(int64_t(n) * j / parts[i]), s1 = int32_t(int64_t(n) * (j + 1) / parts[i]);
+      WorkItem x = w;
+      const auto c = cut(w, s0, s1);
+      x.span_off = c.first;
+      x.span_cnt = c.second;
+      x.slot = parts[i] > 1 ? ++s->slots : 0;
+      out.push_back({s1 - s0, x});
+    }
+  }
+  std::stable_sort(out.begin(), out.end(), [](const auto& a, const auto& b) { return a.first > b.first; });
+  s->items.clear();
+  for (auto& e : out) s->items.push_back(e.second);
+  s->real_items = int64_t(s->items.size());
+  s->spans.swap(spans);
+}
+
+// Sorts v longest first and returns the items' steps.
+std::vector<int32_t> sort_steps(CostedItems& v, const Schedule& s) {
+  std::stable_sort(v.begin(), v.end(), [](const auto& a, const auto& b) { return a.first > b.first; });
+  std::map<std::pair<int32_t, int32_t>, int32_t> known;
+  std::vector<int32_t> steps;
+  for (const auto& e : v) {
+    const auto key = std::make_pair(e.second.span_off, e.second.span_cnt);
+    auto it = known.find(key);
+    if (it == known.end()) {
+      int32_t n = 0;
+      for (int32_t i = 0; i < key.second; ++i) n += span_steps(s.spans[size_t(key.first) + i]);
+      it = known.emplace(key, n).first;
+    }
+    steps.push_back(it->second);
+  }
+  return steps;
+}
+
+// The forward's partial results take no more than kFwdPartialBytes; kTableBytes is more than the
+// tables of any launch that is split (at most 16 rounds of items and their pieces) take.
+constexpr int64_t kTableBytes = int64_t(4) << 20;
+constexpr int64_t kFwdPartialBytes = int64_t(SRA_NOALLOC_WORKSPACE_MAX) - kTableBytes;
+
+// The forward's launch: rows per item and splits by the replayed end. A step of the large tile
+// holds 1.5 (d = 128) or 2 (d = 64) times the rows and takes 1.36 or 1.72 times as long (480p, 40
+// heads: 25.5 -> 23.7 ms; 480p, d = 64, 16 heads: 8.35 -> 7.24 ms). max_bytes: of partial results.
+void launch_forward_schedule(const Layout& L, int64_t max_bytes, Schedule* out) {
+  double best = 0;
+  for (int tile : {kFwdQueryTile, fwd_large_tile(L.head_dim)}) {
+    const bool large = tile != kFwdQueryTile;
+    const KernelCost c{!large ? 1.0 : L.head_dim == 128 ? 1.36 : 1.72, 3.0, large ? 3.0 : 2.0, 4.0};
+    Schedule s;
+    CostedItems v = query_major_items(L, tile, kFwdKeyStep, &s);
+    const std::vector<int32_t> steps = sort_steps(v, s);
+    double end;
+    const std::vector<int32_t> parts = choose_split(steps, c, max_bytes / slot_bytes(tile, L.head_dim, 1, 2), &end);
+    if (large && !(end < 0.99 * best)) continue;
+    best = end;
+    if (std::any_of(parts.begin(), parts.end(), [](int32_t k) { return k > 1; })) split_items(v, parts, &s);
+    else finish_whole(v, L, kFwdKeyStep, false, &s);
+    s.tile = tile;
+    *out = std::move(s);
+  }
 }
 
 }  // namespace
@@ -471,7 +646,7 @@ void compact_layout(const Layout& L, Layout* C, std::vector<int32_t>* gather, st
   }
 }
 
-void build_plan(const Layout& L_in, Plan* plan) {
+void build_plan(const Layout& L_in, Plan* plan, bool whole) {
   plan->layout = L_in;
   plan->compacted = needs_compaction(L_in);
   plan->ref_gather.clear();
@@ -481,9 +656,28 @@ void build_plan(const Layout& L_in, Plan* plan) {
   else
     plan->exec = L_in;
   const Layout& L = plan->exec;
-  build_query_major(L, kFwdQueryTile, kFwdKeyStep, &plan->fwd);
-  build_query_major(L, kDqQueryTile, kDqKeyStep, &plan->dq);
-  build_key_major(L, kDkvKeyTile, kDkvQueryStep, &plan->dkv);
+  plan->fwd = plan->dq = plan->dkv = Schedule();
+  if (whole) {
+    CostedItems v = query_major_items(L, kFwdQueryTile, kFwdKeyStep, &plan->fwd);
+    finish_whole(v, L, kFwdKeyStep, false, &plan->fwd);
+    plan->fwd.tile = kFwdQueryTile;
+  } else {
+    // The partial results and the rest of the forward's workspace stay within the static scratch
+    // of the allocation-free forward wherever the rest does, so that it takes the same calls and
+    // runs the same launch.
+    const int64_t ref = plan->compacted ? L.sum_ref * (L.heads * (8 * int64_t(L.head_dim) + 4) + 4) + L_in.sum_ref * 4 : 0;
+    const int64_t room = int64_t(SRA_NOALLOC_WORKSPACE_MAX) - ref;  // <= 0: it rejects the call anyway
+    launch_forward_schedule(L, room <= 0 ? kFwdPartialBytes : std::max<int64_t>(0, std::min(kFwdPartialBytes, room - kTableBytes)),
+                            &plan->fwd);
+  }
+  {
+    CostedItems v = query_major_items(L, kDqQueryTile, kDqKeyStep, &plan->dq);
+    finish_whole(v, L, kDqKeyStep, false, &plan->dq);
+  }
+  {
+    CostedItems v = key_major_items(L, kDkvKeyTile, kDkvQueryStep, &plan->dkv);
+    finish_whole(v, L, kDkvQueryStep, true, &plan->dkv);
+  }
   plan->fill.clear();
   for (const SampleLayout& sm : L.samples) {  // the gaps between valid ref runs
     int64_t r = 0;

@@ -41,6 +41,10 @@ struct Schedule {
   std::vector<WorkItem> items;
   std::vector<Span> spans;
   int64_t real_items = 0;
+  // launched schedules only
+  std::vector<CombineItem> combine;  // split items
+  int32_t slots = 0;                 // their pieces
+  int32_t tile = 0;                  // rows per work item
 };
 
 // When a token mask splits reference frames into many short runs of valid tokens, tiles cut
@@ -52,7 +56,7 @@ struct Plan {
   Layout layout;                   // as given
   bool compacted = false;          // the schedules index the compacted reference stream
   Layout exec;                     // the layout the schedules index (layout, or its compaction)
-  Schedule fwd, dq, dkv;
+  Schedule fwd, dq, dkv;           // as launched: tile sizes chosen, long items split (build_plan)
   std::vector<FillRange> fill;     // invalid reference rows of exec (none when compacted)
   std::vector<int32_t> ref_gather;   // compacted: packed ref row of each compacted row
   std::vector<int32_t> ref_scatter;  // compacted: compacted row of each packed ref row, or -1
@@ -72,8 +76,18 @@ bool needs_compaction(const Layout& L);
 // gbound) with the row maps between the two reference streams.
 void compact_layout(const Layout& L, Layout* C, std::vector<int32_t>* gather, std::vector<int32_t>* scatter);
 
-// Builds the three schedules and the fill list (on the compacted layout when needed).
-void build_plan(const Layout& L, Plan* plan);
+// Bytes of one piece's partial results: fp32 sums of `tensors` rows x head_dim tiles, plus
+// `stats` fp32 values per row.
+inline int64_t slot_bytes(int64_t tile, int64_t head_dim, int tensors, int stats) {
+  return tile * (head_dim * tensors + stats) * int64_t(sizeof(float));
+}
+
+// Builds what a call launches and the fill list (on the compacted layout when needed). A launch of
+// few, long work items leaves compute units idle: its items are split along their spans and the
+// pieces' partial results combined by another kernel, where a replay of the launch on the compute
+// units says that it ends earlier. `whole`: the three schedules of whole 256-row items instead,
+// in the order that the inspection hooks report.
+void build_plan(const Layout& L, Plan* plan, bool whole = false);
 
 // Pairs per head covered by a schedule (head 0 items only, so per head).
 int64_t covered_pairs(const Schedule& s, bool key_major);

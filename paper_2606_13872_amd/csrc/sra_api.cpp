@@ -52,7 +52,7 @@ struct Blob {
 struct CachedPlan {
   Plan plan;
   uint64_t id = 0;  // unique per plan built by this process
-  Blob fwd;   // fwd items | fwd spans | fill | ref gather | ref scatter
+  Blob fwd;   // fwd items | fwd spans | fill | ref gather | ref scatter | split items
   Blob bwd;   // dq items | dq spans | dkv items | dkv spans | fill | ref gather | ref scatter
 };
 
@@ -85,6 +85,7 @@ class PlanCache {
     put_table(cp->fwd, cp->plan.fill);
     put_table(cp->fwd, cp->plan.ref_gather);
     put_table(cp->fwd, cp->plan.ref_scatter);
+    put_table(cp->fwd, cp->plan.fwd.combine);
     put_table(cp->bwd, cp->plan.dq.items);
     put_table(cp->bwd, cp->plan.dq.spans);
     put_table(cp->bwd, cp->plan.dkv.items);
@@ -261,13 +262,20 @@ bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 
 size_t rows_bytes(const Layout& L, int64_t rows) { return align_up(size_t(rows) * L.heads * L.head_dim * 2); }
 size_t stat_bytes(const Layout& L, int64_t rows) { return align_up(size_t(L.heads) * rows * sizeof(float)); }
 
-// Forward workspace: schedule, then (compacted plans) the compacted ref q, k, v, o and lse.
-size_t fwd_workspace(const CachedPlan& cp) {
+// Partial results of a launch's split items.
+size_t fwd_partials(const Plan& p) {
+  return align_up(size_t(p.fwd.slots * slot_bytes(p.fwd.tile, p.exec.head_dim, 1, 2)));
+}
+
+// Forward workspace: schedule, then (compacted plans) the compacted ref q, k, v, o and lse, then
+// the partial results of split items.
+size_t fwd_partials_at(const CachedPlan& cp) {
   const Layout& E = cp.plan.exec;
   size_t b = cp.fwd.bytes;
   if (cp.plan.compacted) b += 4 * rows_bytes(E, E.sum_ref) + stat_bytes(E, E.sum_ref);
   return b;
 }
+size_t fwd_workspace(const CachedPlan& cp) { return fwd_partials_at(cp) + fwd_partials(cp.plan); }
 // Backward workspace: schedule; -D and the LSE in log2 units per query row of each stream;
 // then (compacted plans) the compacted ref q, k, v, o, do, dq, dk, dv and lse.
 size_t bwd_workspace(const CachedPlan& cp) {
@@ -462,6 +470,8 @@ sra_status forward_call(const sra_problem* p, const void* q_gen, const void* k_g
   a.rows[1] = int32_t(E.sum_ref);
   a.heads = L.heads;
   a.scale_log2 = float(double(L.scale) * 1.4426950408889634);
+  a.part = reinterpret_cast<float*>(ws + fwd_partials_at(*cp));
+  a.tile = P.fwd.tile;
   hipError_t e;
   __bf16* o_c = nullptr;
   float* lse_c = nullptr;
@@ -493,7 +503,12 @@ sra_status forward_call(const sra_problem* p, const void* q_gen, const void* k_g
     a.o[1] = o_c;
     a.lse[1] = lse_c;
   }
-  e = timed(SRA_KERNEL_FORWARD, s, [&] { return launch_forward(a, int(P.fwd.items.size()), L.head_dim, s); });
+  e = timed(SRA_KERNEL_FORWARD, s, [&] {
+    const hipError_t x = launch_forward(a, int(P.fwd.items.size()), L.head_dim, s);
+    if (x != hipSuccess) return x;
+    return launch_forward_combine(a, reinterpret_cast<const CombineItem*>(ws + cp->fwd.offsets[5]),
+                                  int(P.fwd.combine.size()), L.head_dim, s);
+  });
   if (e != hipSuccess) return hip_fail(e, "forward launch");
   if (P.compacted && !L.gen_only) {
     ScatterArgs sc{};
@@ -748,7 +763,7 @@ sra_status sra_schedule_info(const sra_problem* p, int which, int64_t* n_items, 
   sra_status st = make_layout(p, &L, &err);
   if (st != SRA_OK) return fail(st, err);
   Plan P;
-  build_plan(L, &P);
+  build_plan(L, &P, true);
   const Schedule* S = pick(P, which);
   if (!S) return fail(SRA_ERR_INVALID_ARGUMENT, "unknown schedule");
   if (n_items) *n_items = int64_t(S->items.size());
@@ -757,18 +772,9 @@ sra_status sra_schedule_info(const sra_problem* p, int which, int64_t* n_items, 
   return SRA_OK;
 }
 
-sra_status sra_schedule_mask(const sra_problem* p, int which, int32_t sample, uint8_t* out) {
-  g_last_error.clear();
-  Layout L;
-  std::string err;
-  sra_status st = make_layout(p, &L, &err);
-  if (st != SRA_OK) return fail(st, err);
-  if (sample < 0 || sample >= L.batch) return fail(SRA_ERR_INVALID_ARGUMENT, "sample out of range");
-  if (!out) return fail(SRA_ERR_INVALID_ARGUMENT, "out is NULL");
-  Plan P;
-  build_plan(L, &P);
-  const Schedule* S = pick(P, which);
-  if (!S) return fail(SRA_ERR_INVALID_ARGUMENT, "unknown schedule");
+// Counts, per (query, key) of `sample`, the work items of `head` that compute the pair.
+static sra_status expand(const Layout& L, const Plan& P, const Schedule& S, bool key_major, int32_t sample, int32_t head,
+                         uint8_t* out) {
   const SampleLayout& sm = L.samples[sample];
   const int64_t n = sm.G + sm.R;
   std::memset(out, 0, size_t(n * n));
@@ -780,11 +786,10 @@ sra_status sra_schedule_mask(const sra_problem* p, int which, int32_t sample, ui
     }
     return sm.G + (row - sm.ref_off);
   };
-  const bool key_major = which == SRA_SCHED_BWD_DKDV;
-  for (const WorkItem& w : S->items) {
-    if (w.stream < 0 || w.head != 0 || w.sample != sample) continue;
+  for (const WorkItem& w : S.items) {
+    if (w.stream < 0 || w.head != head || w.sample != sample) continue;
     for (int32_t si = 0; si < w.span_cnt; ++si) {
-      const Span& sp = S->spans[w.span_off + si];
+      const Span& sp = S.spans[w.span_off + si];
       // a key-major span may reach only the item's keys [lo, hi)
       const int32_t a0 = sp.keys ? (sp.keys & 0xffff) : 0, a1 = sp.keys ? (sp.keys >> 16) : w.len;
       if (a0 < 0 || a1 > w.len || a0 >= a1) return fail(SRA_ERR_INTERNAL, "span key range outside its item");
@@ -803,6 +808,46 @@ sra_status sra_schedule_mask(const sra_problem* p, int which, int32_t sample, ui
   return SRA_OK;
 }
 
+static sra_status expand_call(const sra_problem* p, int which, int32_t sample, int32_t head, bool whole, uint8_t* out) {
+  g_last_error.clear();
+  Layout L;
+  std::string err;
+  sra_status st = make_layout(p, &L, &err);
+  if (st != SRA_OK) return fail(st, err);
+  if (sample < 0 || sample >= L.batch) return fail(SRA_ERR_INVALID_ARGUMENT, "sample out of range");
+  if (head < 0 || head >= L.heads) return fail(SRA_ERR_INVALID_ARGUMENT, "head out of range");
+  if (!out) return fail(SRA_ERR_INVALID_ARGUMENT, "out is NULL");
+  Plan P;
+  build_plan(L, &P, whole);
+  const Schedule* S = pick(P, which);
+  if (!S) return fail(SRA_ERR_INVALID_ARGUMENT, "unknown schedule");
+  return expand(L, P, *S, which == SRA_SCHED_BWD_DKDV, sample, head, out);
+}
+
+sra_status sra_schedule_mask(const sra_problem* p, int which, int32_t sample, uint8_t* out) {
+  return expand_call(p, which, sample, 0, true, out);
+}
+
+sra_status sra_launch_mask(const sra_problem* p, int which, int32_t sample, int32_t head, uint8_t* out) {
+  return expand_call(p, which, sample, head, false, out);
+}
+
+sra_status sra_launch_info(const sra_problem* p, int which, int64_t* n_items, int64_t* tile, int64_t* split_items) {
+  g_last_error.clear();
+  Layout L;
+  std::string err;
+  sra_status st = make_layout(p, &L, &err);
+  if (st != SRA_OK) return fail(st, err);
+  Plan P;
+  build_plan(L, &P);
+  const Schedule* S = pick(P, which);
+  if (!S) return fail(SRA_ERR_INVALID_ARGUMENT, "unknown schedule");
+  if (n_items) *n_items = S->real_items;
+  if (tile) *tile = S->tile;
+  if (split_items) *split_items = int64_t(S->combine.size());
+  return SRA_OK;
+}
+
 sra_status sra_schedule_export(const sra_problem* p, int which, int32_t* items, int64_t items_capacity,
                                int32_t* spans, int64_t spans_capacity) {
   g_last_error.clear();
@@ -811,7 +856,7 @@ sra_status sra_schedule_export(const sra_problem* p, int which, int32_t* items, 
   sra_status st = make_layout(p, &L, &err);
   if (st != SRA_OK) return fail(st, err);
   Plan P;
-  build_plan(L, &P);
+  build_plan(L, &P, true);
   const Schedule* S = pick(P, which);
   if (!S) return fail(SRA_ERR_INVALID_ARGUMENT, "unknown schedule");
   if (items) {

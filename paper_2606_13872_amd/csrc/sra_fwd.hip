@@ -460,10 +460,18 @@ sra_fwd_kernel(FwdArgs a) {
 
   if (!active) return;
   const int64_t ostride = int64_t(a.heads) * D;
+  float* part = it.slot ? a.part + int64_t(it.slot - 1) * (kWaves * 16 * NQ) * (D + 2) : nullptr;
 #pragma unroll
   for (int qb = 0; qb < NQ; ++qb) {
     const int r = wrow0 + 16 * qb + l16;
     const float lt = quad_sum(st.l[qb]);
+    if (part) {  // a piece of a split item
+      if (r >= it.len) continue;
+#pragma unroll
+      for (int db = 0; db < ND; ++db) *reinterpret_cast<floatx4*>(part + r * D + db * 16 + 4 * g) = st.o[qb][db];
+      if (g == 0) *reinterpret_cast<float2*>(part + kWaves * 16 * NQ * D + 2 * r) = float2{st.m[qb], lt};
+      continue;
+    }
     const float inv = 1.f / lt;
     if (r >= it.len) continue;
     __bf16* orow = a.o[s] + int64_t(it.start + r) * ostride + h * D;
@@ -478,18 +486,64 @@ sra_fwd_kernel(FwdArgs a) {
   }
 }
 
+// Rows of the split items from their pieces: with M the largest of the pieces' running maxima,
+// O = sum_i 2^(m_i - M) O_i / sum_i 2^(m_i - M) l_i, in piece order. D / 4 threads per row.
+template <int D>
+__global__ void __launch_bounds__(kThreads) sra_fwd_combine_kernel(FwdArgs a, const CombineItem* items) {
+  constexpr int TPR = D / 4, RPB = kThreads / TPR;
+  const CombineItem it = items[blockIdx.x];
+  const int r = blockIdx.y * RPB + threadIdx.x / TPR, sub = threadIdx.x % TPR, tile = a.tile;
+  if (r >= it.len) return;
+  const int64_t slot = int64_t(tile) * (D + 2);
+  const float* p = a.part + it.slot0 * slot;
+  float m = -INFINITY;
+  for (int i = 0; i < it.n; ++i) m = fmaxf(m, p[i * slot + int64_t(tile) * D + 2 * r]);
+  floatx4 o = floatx4{};
+  float l = 0.f;
+  for (int i = 0; i < it.n; ++i) {
+    const float2 ml = *reinterpret_cast<const float2*>(p + i * slot + int64_t(tile) * D + 2 * r);
+    const float w = fast_exp2(ml.x - m);
+    l += w * ml.y;
+    o += w * *reinterpret_cast<const floatx4*>(p + i * slot + r * D + 4 * sub);
+  }
+  const float inv = 1.f / l;
+  bf16x4 y;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) y[e] = (__bf16)(o[e] * inv);
+  *reinterpret_cast<bf16x4*>(a.o[it.stream] + (int64_t(it.start + r) * a.heads + it.head) * D + 4 * sub) = y;
+  if (sub == 0) a.lse[it.stream][int64_t(it.head) * a.rows[it.stream] + it.start + r] = (m + log2f(l)) * kLn2;
+}
+
+template <int D, int NQ>
+static void launch_tile(const FwdArgs& a, int n_items, hipStream_t stream) {
+  const dim3 grid(n_items), block(kWaves * 64);
+  if (a.in_stride[0] == a.in_stride[1])
+    hipLaunchKernelGGL((sra_fwd_kernel<D, NQ, 1>), grid, block, 0, stream, a);
+  else
+    hipLaunchKernelGGL((sra_fwd_kernel<D, NQ, 2>), grid, block, 0, stream, a);
+}
+
 hipError_t launch_forward(const FwdArgs& a, int n_items, int head_dim, hipStream_t stream) {
   if (n_items <= 0) return hipSuccess;
-  const bool one = a.in_stride[0] == a.in_stride[1];
-  constexpr int NQ = kFwdQueryTile / 128;
-  const dim3 grid(n_items), block(kWaves * 64);
+  const bool large = a.tile != kFwdQueryTile;
   if (head_dim == 128) {
-    if (one) hipLaunchKernelGGL((sra_fwd_kernel<128, NQ, 1>), grid, block, 0, stream, a);
-    else hipLaunchKernelGGL((sra_fwd_kernel<128, NQ, 2>), grid, block, 0, stream, a);
+    if (large) launch_tile<128, fwd_large_tile(128) / 128>(a, n_items, stream);
+    else launch_tile<128, kFwdQueryTile / 128>(a, n_items, stream);
   } else {
-    if (one) hipLaunchKernelGGL((sra_fwd_kernel<64, NQ, 1>), grid, block, 0, stream, a);
-    else hipLaunchKernelGGL((sra_fwd_kernel<64, NQ, 2>), grid, block, 0, stream, a);
+    if (large) launch_tile<64, fwd_large_tile(64) / 128>(a, n_items, stream);
+    else launch_tile<64, kFwdQueryTile / 128>(a, n_items, stream);
   }
+  return hipGetLastError();
+}
+
+hipError_t launch_forward_combine(const FwdArgs& a, const CombineItem* items, int n, int head_dim, hipStream_t stream) {
+  if (n <= 0) return hipSuccess;
+  const int rows = kThreads / (head_dim / 4);
+  const dim3 grid(n, (a.tile + rows - 1) / rows);
+  if (head_dim == 128)
+    hipLaunchKernelGGL(sra_fwd_combine_kernel<128>, grid, dim3(kThreads), 0, stream, a, items);
+  else
+    hipLaunchKernelGGL(sra_fwd_combine_kernel<64>, grid, dim3(kThreads), 0, stream, a, items);
   return hipGetLastError();
 }
 

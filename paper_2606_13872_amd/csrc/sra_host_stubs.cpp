@@ -7,6 +7,9 @@
 namespace sra {
 
 hipError_t launch_forward(const FwdArgs&, int, int, hipStream_t) { return hipErrorNotSupported; }
+hipError_t launch_forward_combine(const FwdArgs&, const CombineItem*, int, int, hipStream_t) {
+  return hipErrorNotSupported;
+}
 hipError_t launch_delta(const DeltaArgs&, int, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_dq(const BwdArgs&, int, int, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_dkv(const BwdArgs&, int, int, hipStream_t) { return hipErrorNotSupported; }

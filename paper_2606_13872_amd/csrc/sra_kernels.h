@@ -20,6 +20,8 @@ struct FwdArgs {
   int32_t rows[2];       // packed rows per stream
   int32_t heads;
   float scale_log2;      // softmax scale * log2(e)
+  float* part;           // slots of split items: O [tile, D] unscaled, then (m, l) per row
+  int32_t tile;          // rows per work item
 };
 
 struct BwdArgs {
@@ -91,6 +93,7 @@ struct ScatterArgs {
 };
 
 hipError_t launch_forward(const FwdArgs& a, int n_items, int head_dim, hipStream_t stream);
+hipError_t launch_forward_combine(const FwdArgs& a, const CombineItem* items, int n, int head_dim, hipStream_t stream);
 hipError_t launch_delta(const DeltaArgs& a, int head_dim, hipStream_t stream);
 hipError_t launch_dq(const BwdArgs& a, int n_items, int head_dim, hipStream_t stream);
 hipError_t launch_dkv(const BwdArgs& a, int n_items, int head_dim, hipStream_t stream);

@@ -80,6 +80,8 @@ def lib() -> ctypes.CDLL:
         "sra_pair_counts": [P, ctypes.POINTER(i64), ctypes.POINTER(i64)],
         "sra_schedule_info": [P, ctypes.c_int, ctypes.POINTER(i64), ctypes.POINTER(i64), ctypes.POINTER(i64)],
         "sra_schedule_mask": [P, ctypes.c_int, i32, vp],
+        "sra_launch_info": [P, ctypes.c_int, ctypes.POINTER(i64), ctypes.POINTER(i64), ctypes.POINTER(i64)],
+        "sra_launch_mask": [P, ctypes.c_int, i32, i32, vp],
         "sra_dense_mask": [P, i32, vp],
         "sra_schedule_export": [P, ctypes.c_int, vp, i64, vp, i64],
         "sra_release_caches": [],
@@ -236,6 +238,24 @@ def schedule_mask(samples, which: int, sample: int, heads=1, head_dim=128, flags
     n = g.gen_frames * g.gen_h * g.gen_w + g.ref_frames * g.ref_h * g.ref_w
     out = np.zeros((n, n), dtype=np.uint8)
     _check(lib().sra_schedule_mask(p.ptr, which, sample, out.ctypes.data_as(ctypes.c_void_p)))
+    return out
+
+
+def launch_info(samples, which: int, heads=1, head_dim=128, flags=0) -> Tuple[int, int, int]:
+    """(work items and pieces, rows per item, split items) of what a call launches."""
+    p = Problem(samples, heads, head_dim, flags=flags)
+    a, b, c = ctypes.c_int64(0), ctypes.c_int64(0), ctypes.c_int64(0)
+    _check(lib().sra_launch_info(p.ptr, which, ctypes.byref(a), ctypes.byref(b), ctypes.byref(c)))
+    return int(a.value), int(b.value), int(c.value)
+
+
+def launch_mask(samples, which: int, sample: int, head: int, heads=1, head_dim=128, flags=0):
+    """sra_launch_mask: how often a call computes each (query, key) pair of `sample` in `head`."""
+    p = Problem(samples, heads, head_dim, flags=flags)
+    g = p.samples[sample]
+    n = g.gen_frames * g.gen_h * g.gen_w + g.ref_frames * g.ref_h * g.ref_w
+    out = np.zeros((n, n), dtype=np.uint8)
+    _check(lib().sra_launch_mask(p.ptr, which, sample, head, out.ctypes.data_as(ctypes.c_void_p)))
     return out
 
 
