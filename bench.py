@@ -34,7 +34,7 @@ CSRC = os.path.join(ROOT, "paper_2606_13872_amd", "csrc")
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_720p.json")
 KERNEL_SYMBOLS = {"forward": "sra_fwd_kernel", "dkdv": "sra_dkv_kernel", "dq": "sra_dq_kernel",
                   "delta": "sra_delta_kernel"}
-KERNEL_SOURCES = {"forward": ["sra_fwd.hip"], "dkdv": ["sra_dkv.hip"], "dq": ["sra_dq.hip"],
+KERNEL_SOURCES = {"forward": ["sra_fwd.hip"], "dkdv": ["sra_grad.hip", "sra_dkv.h"], "dq": ["sra_grad.hip", "sra_dq.h"],
                   "delta": ["sra_bwd.hip"]}
 # schedule.cpp sets the launch order of the work items, which decides how often a tile is
 # fetched again from HBM

@@ -243,7 +243,8 @@ sra_status sra_schedule_export(const sra_problem* p, int which, int32_t* items,
 enum {
   SRA_KERNEL_FORWARD = 0,   /* forward pass                              */
   SRA_KERNEL_DELTA = 1,     /* backward: D = rowsum(dO * O)              */
-  SRA_KERNEL_DKDV = 2,      /* backward: dK and dV (key-major)           */
+  SRA_KERNEL_DKDV = 2,      /* backward: dK and dV (key-major); with dQ where few items of both
+                             * kinds run as one launch                   */
   SRA_KERNEL_DQ = 3,        /* backward: dQ (query-major)                */
   SRA_KERNEL_FILL = 4,      /* rows of invalid reference frames          */
   SRA_KERNEL_GATHER = 5,    /* reference rows into the compacted stream  */

@@ -18,7 +18,7 @@ CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libsra.so")
 
-SOURCES = ["schedule.cpp", "sra_api.cpp", "sra_fwd.hip", "sra_bwd.hip", "sra_dq.hip", "sra_dkv.hip",
+SOURCES = ["schedule.cpp", "sra_api.cpp", "sra_fwd.hip", "sra_bwd.hip", "sra_grad.hip",
            "sra_compact.hip", "sra_noalloc.hip"]
 
 COMMON = [
@@ -28,10 +28,10 @@ COMMON = [
 # Device code only for gfx950. Packed-FP32 instructions are disabled in device code.
 HIP_FLAGS = ["-x", "hip", "--offload-arch=gfx950", "-Xclang", "-target-feature",
              "-Xclang", "-packed-fp32-ops"]
-# The dK/dV and dQ kernels select their compiler-visible MFMAs in VGPR form: their AGPRs hold
+# The dK/dV and dQ kernels (sra_grad.hip) select their compiler-visible MFMAs in VGPR form: their AGPRs hold
 # the gradient sums (written by inline-assembly MFMAs), and S/dP must stay in VGPRs next to them.
 _VGPR_FORM = ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
-EXTRA_FLAGS = {"sra_dkv.hip": _VGPR_FORM, "sra_dq.hip": _VGPR_FORM}
+EXTRA_FLAGS = {"sra_grad.hip": _VGPR_FORM}
 COMPILE_TIMEOUT_S = 900
 
 

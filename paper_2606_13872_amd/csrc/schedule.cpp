@@ -465,47 +465,58 @@ double makespan(std::vector<double>& t) {
 
 int32_t span_steps(const Span& x) { return (x.len + kStep - 1) / kStep; }
 
-// Pieces per item (same order as `steps`, which is longest first) that end the launch earliest, or
+constexpr int kSplitRounds = 8;
+
+// An item of a launch: its steps, its kernel's times and the bytes of a piece's partial results.
+struct Timed {
+  int32_t steps;
+  const KernelCost* c;
+  int64_t bytes;
+  double time() const { return steps * c->step + c->item; }
+};
+
+// Pieces per item (same order as `v`, which is longest first) that end the launch earliest, or
 // all ones; *end is that time. Tried: every item longer than a part of the longest cut to such
 // parts, and the same for only those items of the long ones that a last, partial round of the
-// compute units would hold. Launches of over 16 rounds lose less than their last round is worth.
-std::vector<int32_t> choose_split(const std::vector<int32_t>& steps, const KernelCost& c, int64_t max_slots,
-                                  double* end) {
-  const size_t n = steps.size();
+// compute units would hold. Not for launches of over kSplitRounds rounds: there the order that keeps
+// items of a head in step on an XCD is worth more than the last round.
+std::vector<int32_t> choose_split(const std::vector<Timed>& v, int64_t max_bytes, double* end) {
+  const size_t n = v.size();
   std::vector<int32_t> best(n, 1), k(n);
-  if (n == 0) return *end = 0, best;
+  *end = 0;
+  if (n == 0) return best;
   double total = 0;
-  for (int32_t x : steps) total += x * c.step + c.item;
-  if (n > size_t(16 * kNumCus)) {
-    *end = total / kNumCus + 0.5 * (steps[0] * c.step + c.item);
+  for (const Timed& x : v) total += x.time();
+  if (n > size_t(kSplitRounds * kNumCus)) {
+    *end = total / kNumCus + 0.5 * v[0].time();
     return best;
   }
   std::vector<double> t;
   auto eval = [&](const std::vector<int32_t>& parts) {
     t.clear();
-    bool any = false;
+    double combine = 0;
     for (size_t i = 0; i < n; ++i) {
-      any |= parts[i] > 1;
+      const KernelCost& c = *v[i].c;
+      if (parts[i] > 1) combine = std::max(combine, c.combine);
       for (int32_t j = 0; j < parts[i]; ++j)
-        t.push_back(double(steps[i]) / parts[i] * c.step + c.item + (parts[i] > 1 ? c.piece : 0));
+        t.push_back(double(v[i].steps) / parts[i] * c.step + c.item + (parts[i] > 1 ? c.piece : 0));
     }
-    return makespan(t) + (any ? c.combine : 0);
+    return makespan(t) + combine;
   };
   *end = eval(best);
-  const double whole = *end;
+  const double whole = *end, longest = v[0].steps * v[0].c->step;
   size_t n_long = 0;
-  while (n_long < n && 2 * steps[n_long] >= steps[0]) ++n_long;
+  while (n_long < n && 2 * v[n_long].time() >= v[0].time()) ++n_long;
   const size_t rounds = n_long / kNumCus * kNumCus;
   for (int32_t parts = 2; parts <= 24; ++parts) {
-    const int32_t piece = std::max<int32_t>(2, (steps[0] + parts - 1) / parts);
     for (int tail = 0; tail < (rounds > 0 ? 2 : 1); ++tail) {
-      const size_t first = tail ? rounds : 0;
-      int64_t slots = 0;
+      int64_t bytes = 0;
       for (size_t i = 0; i < n; ++i) {
-        k[i] = i < first ? 1 : std::max<int32_t>(1, (steps[i] + piece - 1) / piece);
-        if (k[i] > 1) slots += k[i];
+        const double piece = std::max(2.0 * v[i].c->step, longest / parts);  // two steps at least
+        k[i] = i < (tail ? rounds : 0) ? 1 : std::max<int32_t>(1, int32_t(std::ceil(v[i].steps * v[i].c->step / piece - 1e-9)));
+        if (k[i] > 1) bytes += k[i] * v[i].bytes;
       }
-      if (slots == 0 || slots > max_slots) continue;
+      if (bytes == 0 || bytes > max_bytes) continue;
       const double e = eval(k);
       if (e < *end && e < 0.97 * whole) {
         *end = e;
@@ -516,8 +527,21 @@ std::vector<int32_t> choose_split(const std::vector<int32_t>& steps, const Kerne
   return best;
 }
 
-// Replaces the items of v (longest first, with their spans in s) by their pieces, into s.
-void split_items(const CostedItems& v, const std::vector<int32_t>& parts, Schedule* s) {
+// Steps of an item: of its gen spans (which come first) and of the others.
+std::pair<int32_t, int32_t> item_steps(const WorkItem& w, const Schedule& s) {
+  std::pair<int32_t, int32_t> n{0, 0};
+  for (int32_t i = 0; i < w.span_cnt; ++i) {
+    const Span& x = s.spans[size_t(w.span_off) + i];
+    (x.stream == 0 ? n.first : n.second) += span_steps(x);
+  }
+  return n;
+}
+
+// Replaces the items of v (longest first, with their spans in s) by their pieces, into s: parts[i] of
+// the item's steps; or with `own_ref` of the steps of its gen spans alone, its ref spans going with
+// the last of them, or as pieces of their own where they are longer than such a piece. (A key
+// tile's gen queries are then cut the same way whether or not the ref queries are computed.)
+void split_items(const CostedItems& v, const std::vector<int32_t>& parts, bool own_ref, Schedule* s) {
   std::vector<Span> spans;
   std::map<std::pair<int32_t, std::pair<int32_t, int32_t>>, std::pair<int32_t, int32_t>> made;
   std::vector<std::pair<int32_t, WorkItem>> out;
@@ -536,21 +560,29 @@ void split_items(const CostedItems& v, const std::vector<int32_t>& parts, Schedu
     }
     return made[key] = {off, int32_t(spans.size()) - off};
   };
+  std::vector<int32_t> ends;
   for (size_t i = 0; i < v.size(); ++i) {
-    WorkItem w = v[i].second;
-    int32_t n = 0;
-    for (int32_t j = 0; j < w.span_cnt; ++j) n += span_steps(s->spans[size_t(w.span_off) + j]);
-    if (parts[i] > 1) {
-      s->combine.push_back({w.stream, w.head, w.start, w.len, s->slots, parts[i], {0, 0}});
+    const WorkItem& w = v[i].second;
+    const auto n = item_steps(w, *s);
+    const int32_t all = n.first + n.second, body = own_ref && n.first > 0 ? n.first : all;
+    ends.clear();
+    for (int32_t j = 1; j <= parts[i]; ++j) ends.push_back(int32_t(int64_t(body) * j / parts[i]));
+    if (body < all) {
+      const int32_t piece = (body + parts[i] - 1) / parts[i], extra = parts[i] > 1 ? (all - body) / piece : 0;
+      if (extra == 0) ends.back() = all;
+      for (int32_t j = 1; j <= extra; ++j) ends.push_back(body + int32_t(int64_t(all - body) * j / extra));
     }
-    for (int32_t j = 0; j < parts[i]; ++j) {
-      const int32_t s0 = int32_t(int64_t(n) * j / parts[i]), s1 = int32_t(int64_t(n) * (j + 1) / parts[i]);
+    const int32_t k = int32_t(ends.size());
+    if (k > 1) s->combine.push_back({w.stream, w.head, w.start, w.len, s->slots, k, {0, 0}});
+    int32_t from = 0;
+    for (int32_t to : ends) {
       WorkItem x = w;
-      const auto c = cut(w, s0, s1);
+      const auto c = cut(w, from, to);
       x.span_off = c.first;
       x.span_cnt = c.second;
-      x.slot = parts[i] > 1 ? ++s->slots : 0;
-      out.push_back({s1 - s0, x});
+      x.slot = k > 1 ? ++s->slots : 0;
+      out.push_back({to - from, x});
+      from = to;
     }
   }
   std::stable_sort(out.begin(), out.end(), [](const auto& a, const auto& b) { return a.first > b.first; });
@@ -579,7 +611,7 @@ std::vector<int32_t> sort_steps(CostedItems& v, const Schedule& s) {
 }
 
 // The forward's partial results take no more than kFwdPartialBytes; kTableBytes is more than the
-// tables of any launch that is split (at most 16 rounds of items and their pieces) take.
+// tables of any launch that is split (at most kSplitRounds rounds of items and their pieces) take.
 constexpr int64_t kTableBytes = int64_t(4) << 20;
 constexpr int64_t kFwdPartialBytes = int64_t(SRA_NOALLOC_WORKSPACE_MAX) - kTableBytes;
 
@@ -587,22 +619,126 @@ constexpr int64_t kFwdPartialBytes = int64_t(SRA_NOALLOC_WORKSPACE_MAX) - kTable
 // holds 1.5 (d = 128) or 2 (d = 64) times the rows and takes 1.36 or 1.72 times as long (480p, 40
 // heads: 25.5 -> 23.7 ms; 480p, d = 64, 16 heads: 8.35 -> 7.24 ms). max_bytes: of partial results.
 void launch_forward_schedule(const Layout& L, int64_t max_bytes, Schedule* out) {
+  Layout all = L;
+  all.gen_only = false;
   double best = 0;
   for (int tile : {kFwdQueryTile, fwd_large_tile(L.head_dim)}) {
     const bool large = tile != kFwdQueryTile;
     const KernelCost c{!large ? 1.0 : L.head_dim == 128 ? 1.36 : 1.72, 3.0, large ? 3.0 : 2.0, 4.0};
     Schedule s;
-    CostedItems v = query_major_items(L, tile, kFwdKeyStep, &s);
+    CostedItems v = query_major_items(all, tile, kFwdKeyStep, &s);
     const std::vector<int32_t> steps = sort_steps(v, s);
+    std::vector<Timed> timed;
+    for (int32_t n : steps) timed.push_back({n, &c, slot_bytes(tile, L.head_dim, 1, 2)});
     double end;
-    const std::vector<int32_t> parts = choose_split(steps, c, max_bytes / slot_bytes(tile, L.head_dim, 1, 2), &end);
+    std::vector<int32_t> parts = choose_split(timed, max_bytes, &end);
     if (large && !(end < 0.99 * best)) continue;
     best = end;
-    if (std::any_of(parts.begin(), parts.end(), [](int32_t k) { return k > 1; })) split_items(v, parts, &s);
-    else finish_whole(v, L, kFwdKeyStep, false, &s);
+    if (L.gen_only) {  // the gen rows' items, as in the call of all rows
+      size_t n = 0;
+      for (size_t i = 0; i < v.size(); ++i)
+        if (v[i].second.stream == 0) {
+          v[n] = v[i];
+          parts[n++] = parts[i];
+        }
+      v.resize(n);
+      parts.resize(n);
+    }
+    if (std::any_of(parts.begin(), parts.end(), [](int32_t k) { return k > 1; })) {
+      split_items(v, parts, false, &s);
+    } else {
+      finish_whole(v, L, kFwdKeyStep, false, &s);
+    }
     s.tile = tile;
     *out = std::move(s);
   }
+}
+
+// The backward's launches. Times in units of 0.75 us (a dQ step takes 2.25 us, a dK/dV step 3.0, a
+// launch and its first tile about 6): up to kSplitRounds rounds of items run as one launch,
+// split where that ends earlier; longer launches run kind by kind, each in its own order.
+constexpr int64_t kBwdPartialBytes = int64_t(256) << 20;
+const KernelCost kDkvCost{4.0, 8.0, 8.0, 8.0}, kDqCost{3.0, 8.0, 5.0, 8.0};
+
+void launch_backward_schedules(const Layout& L, Plan* plan) {
+  // Whether and how items are split is settled for the call of all rows, so that the gradients of
+  // the gen rows and of the keys do not depend on whether the ref queries are computed.
+  Layout full = L;
+  full.gen_only = false;
+  Schedule dq, dkv;
+  CostedItems vq = query_major_items(full, kDqQueryTile, kDqKeyStep, &dq);
+  CostedItems vk = key_major_items(full, kDkvKeyTile, kDkvQueryStep, &dkv);
+  dq.tile = kDqQueryTile;
+  dkv.tile = kDkvKeyTile;
+  if (vq.size() + vk.size() > size_t(kSplitRounds * kNumCus)) {
+    if (L.gen_only) {
+      dq = dkv = Schedule();
+      vq = query_major_items(L, kDqQueryTile, kDqKeyStep, &dq);
+      vk = key_major_items(L, kDkvKeyTile, kDkvQueryStep, &dkv);
+      dq.tile = kDqQueryTile;
+      dkv.tile = kDkvKeyTile;
+    }
+    finish_whole(vq, L, kDqKeyStep, false, &dq);
+    finish_whole(vk, L, kDkvQueryStep, true, &dkv);
+    plan->dq = std::move(dq);
+    plan->dkv = std::move(dkv);
+    return;
+  }
+  // entry i < vk.size(): key item i, else query item i - vk.size()
+  const std::vector<int32_t> sk = sort_steps(vk, dkv), sq = sort_steps(vq, dq);
+  std::vector<Timed> timed, sorted;
+  for (int32_t n : sk) timed.push_back({n, &kDkvCost, slot_bytes(kDkvKeyTile, L.head_dim, 2, 0)});
+  for (int32_t n : sq) timed.push_back({n, &kDqCost, slot_bytes(kDqQueryTile, L.head_dim, 1, 0)});
+  std::vector<int32_t> order(timed.size());
+  std::iota(order.begin(), order.end(), 0);
+  std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return timed[a].time() > timed[b].time(); });
+  for (int32_t i : order) sorted.push_back(timed[i]);
+  double end;
+  const std::vector<int32_t> k = choose_split(sorted, kBwdPartialBytes, &end);
+  std::vector<int32_t> pk(vk.size()), pq(vq.size());
+  for (size_t i = 0; i < order.size(); ++i) {
+    if (size_t(order[i]) < vk.size()) pk[order[i]] = k[i];
+    else pq[order[i] - vk.size()] = k[i];
+  }
+  if (L.gen_only) {
+    size_t n = 0;
+    for (size_t i = 0; i < vq.size(); ++i)
+      if (vq[i].second.stream == 0) {
+        vq[n] = vq[i];
+        pq[n++] = pq[i];
+      }
+    vq.resize(n);
+    pq.resize(n);
+    for (auto& e : vk) {  // the gen queries' spans come first
+      int32_t m = 0;
+      while (m < e.second.span_cnt && dkv.spans[size_t(e.second.span_off) + m].stream == 0) ++m;
+      e.second.span_cnt = m;
+    }
+  }
+  split_items(vk, pk, true, &dkv);
+  split_items(vq, pq, false, &dq);
+  Schedule& g = plan->grad;
+  std::vector<std::pair<double, WorkItem>> all;
+  auto add = [&](const Schedule& s, const KernelCost& c, int32_t mark) {
+    const int32_t base = int32_t(g.spans.size());
+    g.spans.insert(g.spans.end(), s.spans.begin(), s.spans.end());
+    for (WorkItem w : s.items) {
+      int32_t n = 0;
+      for (int32_t i = 0; i < w.span_cnt; ++i) n += span_steps(s.spans[size_t(w.span_off) + i]);
+      w.span_off += base;
+      w.stream |= mark;
+      all.push_back({n * c.step + c.item, w});
+    }
+    g.combine.insert(g.combine.end(), s.combine.begin(), s.combine.end());
+  };
+  add(dkv, kDkvCost, 0);
+  add(dq, kDqCost, 2);
+  std::stable_sort(all.begin(), all.end(), [](const auto& a, const auto& b) { return a.first > b.first; });
+  for (auto& e : all) g.items.push_back(e.second);
+  g.real_items = int64_t(g.items.size());
+  plan->grad_joint = true;
+  plan->dq = std::move(dq);
+  plan->dkv = std::move(dkv);
 }
 
 }  // namespace
@@ -670,13 +806,15 @@ void build_plan(const Layout& L_in, Plan* plan, bool whole) {
     launch_forward_schedule(L, room <= 0 ? kFwdPartialBytes : std::max<int64_t>(0, std::min(kFwdPartialBytes, room - kTableBytes)),
                             &plan->fwd);
   }
-  {
-    CostedItems v = query_major_items(L, kDqQueryTile, kDqKeyStep, &plan->dq);
-    finish_whole(v, L, kDqKeyStep, false, &plan->dq);
-  }
-  {
-    CostedItems v = key_major_items(L, kDkvKeyTile, kDkvQueryStep, &plan->dkv);
-    finish_whole(v, L, kDkvQueryStep, true, &plan->dkv);
+  plan->grad_joint = false;
+  plan->grad = Schedule();
+  if (whole) {
+    CostedItems vq = query_major_items(L, kDqQueryTile, kDqKeyStep, &plan->dq);
+    finish_whole(vq, L, kDqKeyStep, false, &plan->dq);
+    CostedItems vk = key_major_items(L, kDkvKeyTile, kDkvQueryStep, &plan->dkv);
+    finish_whole(vk, L, kDkvQueryStep, true, &plan->dkv);
+  } else {
+    launch_backward_schedules(L, plan);
   }
   plan->fill.clear();
   for (const SampleLayout& sm : L.samples) {  // the gaps between valid ref runs

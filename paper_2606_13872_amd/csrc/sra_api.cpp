@@ -53,7 +53,9 @@ struct CachedPlan {
   Plan plan;
   uint64_t id = 0;  // unique per plan built by this process
   Blob fwd;   // fwd items | fwd spans | fill | ref gather | ref scatter | split items
-  Blob bwd;   // dq items | dq spans | dkv items | dkv spans | fill | ref gather | ref scatter
+  // dq items | dq spans | dkv items | dkv spans | fill | ref gather | ref scatter, or with one
+  // launch for both: nothing | nothing | items | spans | fill | ref gather | ref scatter | split items
+  Blob bwd;
 };
 
 template <class T>
@@ -86,13 +88,17 @@ class PlanCache {
     put_table(cp->fwd, cp->plan.ref_gather);
     put_table(cp->fwd, cp->plan.ref_scatter);
     put_table(cp->fwd, cp->plan.fwd.combine);
-    put_table(cp->bwd, cp->plan.dq.items);
-    put_table(cp->bwd, cp->plan.dq.spans);
-    put_table(cp->bwd, cp->plan.dkv.items);
-    put_table(cp->bwd, cp->plan.dkv.spans);
+    const bool joint = cp->plan.grad_joint;
+    const Schedule none;
+    const Schedule &first = joint ? none : cp->plan.dq, &second = joint ? cp->plan.grad : cp->plan.dkv;
+    put_table(cp->bwd, first.items);
+    put_table(cp->bwd, first.spans);
+    put_table(cp->bwd, second.items);
+    put_table(cp->bwd, second.spans);
     put_table(cp->bwd, cp->plan.fill);
     put_table(cp->bwd, cp->plan.ref_gather);
     put_table(cp->bwd, cp->plan.ref_scatter);
+    put_table(cp->bwd, cp->plan.grad.combine);
     if (map_.size() >= kMaxPlans) evict_one();
     lru_.push_front(key);
     map_[key] = {cp, lru_.begin()};
@@ -277,13 +283,21 @@ size_t fwd_partials_at(const CachedPlan& cp) {
 }
 size_t fwd_workspace(const CachedPlan& cp) { return fwd_partials_at(cp) + fwd_partials(cp.plan); }
 // Backward workspace: schedule; -D and the LSE in log2 units per query row of each stream;
-// then (compacted plans) the compacted ref q, k, v, o, do, dq, dk, dv and lse.
-size_t bwd_workspace(const CachedPlan& cp) {
+// then (compacted plans) the compacted ref q, k, v, o, do, dq, dk, dv and lse; then the partial
+// results of split dK/dV items and of split dQ items.
+size_t kv_partials(const Plan& p) {
+  return align_up(size_t(p.dkv.slots * slot_bytes(kDkvKeyTile, p.exec.head_dim, 2, 0)));
+}
+size_t q_partials(const Plan& p) {
+  return align_up(size_t(p.dq.slots * slot_bytes(kDqQueryTile, p.exec.head_dim, 1, 0)));
+}
+size_t bwd_partials_at(const CachedPlan& cp) {
   const Layout& E = cp.plan.exec;
   size_t b = cp.bwd.bytes + 2 * stat_bytes(E, E.sum_gen) + 2 * stat_bytes(E, E.sum_ref);
   if (cp.plan.compacted) b += 8 * rows_bytes(E, E.sum_ref) + stat_bytes(E, E.sum_ref);
   return b;
 }
+size_t bwd_workspace(const CachedPlan& cp) { return bwd_partials_at(cp) + kv_partials(cp.plan) + q_partials(cp.plan); }
 
 sra_status common_checks(const sra_problem* p, Layout* L, std::shared_ptr<CachedPlan>* cp) {
   std::string err;
@@ -669,14 +683,27 @@ sra_status sra_backward(const sra_problem* p, const void* q_gen, const void* k_g
   a.scale = L.scale;
   a.scale_log2 = float(double(L.scale) * 1.4426950408889634);
 
+  a.part_kv = reinterpret_cast<float*>(ws + bwd_partials_at(*cp));
+  a.part_q = reinterpret_cast<float*>(ws + bwd_partials_at(*cp) + kv_partials(P));
+
   a.items = reinterpret_cast<const WorkItem*>(ws + cp->bwd.offsets[2]);
   a.spans = reinterpret_cast<const Span*>(ws + cp->bwd.offsets[3]);
-  e = timed(SRA_KERNEL_DKDV, s, [&] { return launch_dkv(a, int(P.dkv.items.size()), L.head_dim, s); });
-  if (e != hipSuccess) return hip_fail(e, "dkv launch");
-  a.items = reinterpret_cast<const WorkItem*>(ws + cp->bwd.offsets[0]);
-  a.spans = reinterpret_cast<const Span*>(ws + cp->bwd.offsets[1]);
-  e = timed(SRA_KERNEL_DQ, s, [&] { return launch_dq(a, int(P.dq.items.size()), L.head_dim, s); });
-  if (e != hipSuccess) return hip_fail(e, "dq launch");
+  if (P.grad_joint) {
+    e = timed(SRA_KERNEL_DKDV, s, [&] {
+      const hipError_t x = launch_grad(GradKind::kBoth, a, int(P.grad.items.size()), L.head_dim, s);
+      if (x != hipSuccess) return x;
+      return launch_grad_combine(a, reinterpret_cast<const CombineItem*>(ws + cp->bwd.offsets[7]),
+                                 int(P.dkv.combine.size()), int(P.grad.combine.size()), L.head_dim, s);
+    });
+    if (e != hipSuccess) return hip_fail(e, "gradient launch");
+  } else {
+    e = timed(SRA_KERNEL_DKDV, s, [&] { return launch_grad(GradKind::kDkv, a, int(P.dkv.items.size()), L.head_dim, s); });
+    if (e != hipSuccess) return hip_fail(e, "dkv launch");
+    a.items = reinterpret_cast<const WorkItem*>(ws + cp->bwd.offsets[0]);
+    a.spans = reinterpret_cast<const Span*>(ws + cp->bwd.offsets[1]);
+    e = timed(SRA_KERNEL_DQ, s, [&] { return launch_grad(GradKind::kDq, a, int(P.dq.items.size()), L.head_dim, s); });
+    if (e != hipSuccess) return hip_fail(e, "dq launch");
+  }
   if (!P.fill.empty()) {
     FillArgs f{};
     f.ranges = reinterpret_cast<const FillRange*>(ws + cp->bwd.offsets[4]);

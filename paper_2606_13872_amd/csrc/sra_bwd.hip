@@ -7,8 +7,8 @@
 // Three kernels, all deterministic (no atomics):
 //   delta : -D and the log-sum-exp in log2 units for every query row (HBM bound); the other
 //           two kernels fetch both per row and use them without further arithmetic.
-//   dq    : query-major, in sra_dq.hip.
-//   dkv   : key-major, in sra_dkv.hip.
+//   dq    : query-major, in sra_dq.h.
+//   dkv   : key-major, in sra_dkv.h.
 // P is recomputed from the forward's log-sum-exp. Spans' ragged ends, and in dK/dV the keys of
 // a tile outside a span's key range, are the only masks.
 #include "sra_kernels.h"
@@ -21,11 +21,13 @@ constexpr float kLog2e = 1.44269504088896340736f;
 }
 
 // --------------------------------------------------------------------------- delta
+// Blocks [0, blocks0) take the gen rows, the others the ref rows.
 template <int D>
-__global__ void __launch_bounds__(kThreads) sra_delta_kernel(DeltaArgs a, int s) {
+__global__ void __launch_bounds__(kThreads) sra_delta_kernel(DeltaArgs a, unsigned blocks0) {
   constexpr int TPR = D / 8;                  // threads per (row, head)
   constexpr int RPB = kThreads / TPR;         // (row, head) pairs per block
-  const int64_t pair = int64_t(blockIdx.x) * RPB + threadIdx.x / TPR;
+  const int s = blockIdx.x >= blocks0;
+  const int64_t pair = int64_t(blockIdx.x - (s ? blocks0 : 0)) * RPB + threadIdx.x / TPR;
   const int64_t total = int64_t(a.rows[s]) * a.heads;
   const int sub = threadIdx.x % TPR;
   float acc = 0.f;
@@ -50,16 +52,14 @@ __global__ void __launch_bounds__(kThreads) sra_delta_kernel(DeltaArgs a, int s)
 }
 
 hipError_t launch_delta(const DeltaArgs& a, int head_dim, hipStream_t stream) {
-  for (int s = 0; s < 2; ++s) {
-    const int64_t total = int64_t(a.rows[s]) * a.heads;
-    if (total == 0) continue;
-    const int rpb = kThreads / (head_dim / 8);
-    const unsigned blocks = unsigned((total + rpb - 1) / rpb);
-    if (head_dim == 128)
-      hipLaunchKernelGGL(sra_delta_kernel<128>, dim3(blocks), dim3(kThreads), 0, stream, a, s);
-    else
-      hipLaunchKernelGGL(sra_delta_kernel<64>, dim3(blocks), dim3(kThreads), 0, stream, a, s);
-  }
+  const int rpb = kThreads / (head_dim / 8);
+  auto blocks = [&](int s) { return unsigned((int64_t(a.rows[s]) * a.heads + rpb - 1) / rpb); };
+  const unsigned b0 = blocks(0), n = b0 + blocks(1);
+  if (n == 0) return hipSuccess;
+  if (head_dim == 128)
+    hipLaunchKernelGGL(sra_delta_kernel<128>, dim3(n), dim3(kThreads), 0, stream, a, b0);
+  else
+    hipLaunchKernelGGL(sra_delta_kernel<64>, dim3(n), dim3(kThreads), 0, stream, a, b0);
   return hipGetLastError();
 }
 

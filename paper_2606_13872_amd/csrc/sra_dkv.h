@@ -1,4 +1,4 @@
-// dK/dV kernel of the SRA backward on gfx950 (the gradient is described in sra_bwd.hip).
+// dK/dV work items of the SRA backward on gfx950 (the gradient is described in sra_bwd.hip).
 //
 // Key-major: a work item is a tile of 256 keys of one stream and head; its four waves (one per
 // SIMD) own 64 keys each, as four 16-key MFMA blocks, and keep those keys' V, and the first 64
@@ -14,18 +14,17 @@
 // runs behind the next half's S product, so that it hides half of the exponentials (dP the
 // others, dV the dS). Built with MFMAs in VGPR form (S and dP live in VGPRs); the dK/dV
 // products are written as AGPR-accumulating MFMAs (mfma16_agpr).
+#pragma once
 #include "sra_kernels.h"
 #include "sra_tiles.h"
 
 namespace sra {
 
-namespace {
 constexpr int kDkvWaves = kDkvKeyTile / 64;  // one wave per SIMD, 64 keys each
 constexpr int kDkvTile = 64;                 // queries per LDS tile
 constexpr int kDkvBufs = 3;
 constexpr int kDkvLook = 2;                  // LDS fragments are read this many groups of four MFMAs ahead
 constexpr int kRegChunks = 2;                // 32-dim chunks of K held in registers
-}  // namespace
 
 template <int D>
 struct DkvState {
@@ -317,22 +316,18 @@ __device__ __forceinline__ void dkv_spans(const BwdArgs& a, const WorkItem& it, 
   }
 }
 
-// kOneStride: gen and ref q share one token stride, so one load offset serves both.
+// One work item; `lds` holds DkvLds<D>::kBytes. kOneStride: gen and ref q share one token stride, so
+// one load offset serves both.
 template <int D, bool kOneStride>
-__global__ void __launch_bounds__(kDkvWaves * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
-sra_dkv_kernel(BwdArgs a) {
+__device__ __forceinline__ void dkv_item(const BwdArgs& a, const WorkItem& it, const unsigned char* lds) {
   constexpr int NC = D / 32, ND = D / 16;
   using L = DkvLds<D>;
-  __shared__ __attribute__((aligned(1024))) unsigned char lds[L::kBytes];
-
-  const WorkItem it = a.items[blockIdx.x];
-  if (it.stream < 0) return;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 4, l16 = lane & 15;
   const int h = it.head, s = it.stream;
   const bool active = wave * 64 < it.len;
   const int64_t dstride = int64_t(a.heads) * D;
-  const uint32_t lds0 = lds_addr(&lds[0]), kl0 = lds0 + kDkvBufs * L::kBuf;
+  const uint32_t lds0 = lds_addr(lds), kl0 = lds0 + kDkvBufs * L::kBuf;
 
   // the item's keys: V and K fragments into VGPRs, K's upper head dims into LDS as a 64-dim tile
   // (rows clamped at the tile end)
@@ -378,10 +373,20 @@ sra_dkv_kernel(BwdArgs a) {
     for (int db = 0; db < ND; ++db) asm volatile("" : "+a"(st.dk[kb][db]), "+a"(st.dv[kb][db]));
 
   if (!active) return;
+  float* part = it.slot ? a.part_kv + int64_t(it.slot - 1) * 2 * kDkvKeyTile * D : nullptr;
 #pragma unroll
   for (int kb = 0; kb < 4; ++kb) {
     const int r = wave * 64 + 16 * kb + l16;
     if (r >= it.len) continue;
+    if (part) {  // a piece of a split item
+      float* p = part + r * D + 4 * g;
+#pragma unroll
+      for (int db = 0; db < ND; ++db) {
+        *reinterpret_cast<floatx4*>(p + db * 16) = st.dk[kb][db];
+        *reinterpret_cast<floatx4*>(p + kDkvKeyTile * D + db * 16) = st.dv[kb][db];
+      }
+      continue;
+    }
     __bf16* kout = a.dk[s] + int64_t(it.start + r) * dstride + h * D;
     __bf16* vout = a.dv[s] + int64_t(it.start + r) * dstride + h * D;
 #pragma unroll
@@ -396,20 +401,6 @@ sra_dkv_kernel(BwdArgs a) {
       *reinterpret_cast<bf16x4*>(vout + db * 16 + 4 * g) = wv;
     }
   }
-}
-
-hipError_t launch_dkv(const BwdArgs& a, int n_items, int head_dim, hipStream_t stream) {
-  if (n_items <= 0) return hipSuccess;
-  const bool one = a.in_stride[0] == a.in_stride[1];
-  const dim3 grid(n_items), block(kDkvWaves * 64);
-  if (head_dim == 128) {
-    if (one) hipLaunchKernelGGL((sra_dkv_kernel<128, true>), grid, block, 0, stream, a);
-    else hipLaunchKernelGGL((sra_dkv_kernel<128, false>), grid, block, 0, stream, a);
-  } else {
-    if (one) hipLaunchKernelGGL((sra_dkv_kernel<64, true>), grid, block, 0, stream, a);
-    else hipLaunchKernelGGL((sra_dkv_kernel<64, false>), grid, block, 0, stream, a);
-  }
-  return hipGetLastError();
 }
 
 }  // namespace sra

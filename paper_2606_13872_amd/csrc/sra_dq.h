@@ -1,4 +1,4 @@
-// dQ kernel of the SRA backward on gfx950 (the gradient is described in sra_bwd.hip).
+// dQ work items of the SRA backward on gfx950 (the gradient is described in sra_bwd.hip).
 //
 // Query-major, like the forward: a work item is a tile of 256 query rows of one stream and
 // head; its four waves (one per SIMD) own 64 rows each, as four 16-row MFMA blocks, and keep
@@ -10,17 +10,16 @@
 // runs behind the next half's S product, so that every product has vector work to hide: dS of
 // the half before during S, the exponentials during dQ and dP. Built with MFMAs in VGPR form;
 // the dQ products are AGPR-accumulating MFMAs (mfma16_agpr).
+#pragma once
 #include "sra_kernels.h"
 #include "sra_tiles.h"
 
 namespace sra {
 
-namespace {
 constexpr int kDqWaves = kDqQueryTile / 64;  // one wave per SIMD, 64 query rows each
 constexpr int kDqTile = 64;                  // keys per LDS tile
 constexpr int kDqBufs = 4;
 constexpr int kDqLook = 2;   // LDS fragments are read this many groups of four MFMAs ahead
-}  // namespace
 
 template <int D>
 struct DqState {
@@ -177,21 +176,21 @@ __device__ __forceinline__ void dq_masked(DqState<D>& st, const DqAddr& ad, uint
   dq_flush<D>(st, ad, kt);
 }
 
-// kOneStride: the streams share one token stride, so one load offset serves both.
+template <int D>
+constexpr uint32_t kDqLdsBytes = kDqBufs * 2 * SwzTile<D, kDqTile>::kElems * 2;
+
+// One work item; `lds` holds kDqLdsBytes<D>. kOneStride: the streams share one token stride, so one
+// load offset serves both.
 template <int D, bool kOneStride>
-__global__ void __launch_bounds__(kDqWaves * 64) __attribute__((amdgpu_waves_per_eu(1, 1)))
-sra_dq_kernel(BwdArgs a) {
+__device__ __forceinline__ void dq_item(const BwdArgs& a, const WorkItem& it, const unsigned char* lds) {
   constexpr int NC = D / 32, ND = D / 16, BK = kDqTile, NB = kDqBufs;
   using TL = SwzTile<D, BK>;
   constexpr uint32_t kTileBytes = TL::kElems * 2;
   constexpr int kLoads = TL::kInstr / kDqWaves;  // of K, and of V, per wave and tile
-  __shared__ __attribute__((aligned(1024))) __bf16 kv[NB][2][TL::kElems];
 
-  const WorkItem it = a.items[blockIdx.x];
-  if (it.stream < 0) return;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 4, l16 = lane & 15;
-  const int h = it.head, s = it.stream;
+  const int h = it.head, s = it.stream & 1;
   const bool active = wave * 64 < it.len;
   const float sl2 = a.scale_log2;
   const int64_t dstride = int64_t(a.heads) * D;
@@ -209,7 +208,7 @@ sra_dq_kernel(BwdArgs a) {
   uint32_t voff[kOneStride ? 1 : 2];
 #pragma unroll
   for (int ss = 0; ss < (kOneStride ? 1 : 2); ++ss) voff[ss] = swz_load_off<D>(a.in_stride[ss], h, wave);
-  const uint32_t lds0 = lds_addr(&kv[0][0][0]);
+  const uint32_t lds0 = lds_addr(lds);
 
   // the pending tile load: bases and LDS address of this wave's instructions
   uint64_t lk = 0, lv = 0, lstep = 0;
@@ -328,10 +327,16 @@ sra_dq_kernel(BwdArgs a) {
     for (int db = 0; db < ND; ++db) asm volatile("" : "+a"(st.dq[qb][db]));
 
   if (!active) return;
+  float* part = it.slot ? a.part_q + int64_t(it.slot - 1) * kDqQueryTile * D : nullptr;
 #pragma unroll
   for (int qb = 0; qb < 4; ++qb) {
     const int r = wave * 64 + 16 * qb + l16;
     if (r >= it.len) continue;
+    if (part) {  // a piece of a split item
+#pragma unroll
+      for (int db = 0; db < ND; ++db) *reinterpret_cast<floatx4*>(part + r * D + db * 16 + 4 * g) = st.dq[qb][db];
+      continue;
+    }
     __bf16* orow = a.dq[s] + int64_t(it.start + r) * dstride + h * D;
 #pragma unroll
     for (int db = 0; db < ND; ++db) {
@@ -341,20 +346,6 @@ sra_dq_kernel(BwdArgs a) {
       *reinterpret_cast<bf16x4*>(orow + db * 16 + 4 * g) = w;
     }
   }
-}
-
-hipError_t launch_dq(const BwdArgs& a, int n_items, int head_dim, hipStream_t stream) {
-  if (n_items <= 0) return hipSuccess;
-  const bool one = a.in_stride[0] == a.in_stride[1];
-  const dim3 grid(n_items), block(kDqWaves * 64);
-  if (head_dim == 128) {
-    if (one) hipLaunchKernelGGL((sra_dq_kernel<128, true>), grid, block, 0, stream, a);
-    else hipLaunchKernelGGL((sra_dq_kernel<128, false>), grid, block, 0, stream, a);
-  } else {
-    if (one) hipLaunchKernelGGL((sra_dq_kernel<64, true>), grid, block, 0, stream, a);
-    else hipLaunchKernelGGL((sra_dq_kernel<64, false>), grid, block, 0, stream, a);
-  }
-  return hipGetLastError();
 }
 
 }  // namespace sra

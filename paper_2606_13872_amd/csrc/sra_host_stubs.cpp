@@ -11,8 +11,10 @@ hipError_t launch_forward_combine(const FwdArgs&, const CombineItem*, int, int, 
   return hipErrorNotSupported;
 }
 hipError_t launch_delta(const DeltaArgs&, int, hipStream_t) { return hipErrorNotSupported; }
-hipError_t launch_dq(const BwdArgs&, int, int, hipStream_t) { return hipErrorNotSupported; }
-hipError_t launch_dkv(const BwdArgs&, int, int, hipStream_t) { return hipErrorNotSupported; }
+hipError_t launch_grad(GradKind, const BwdArgs&, int, int, hipStream_t) { return hipErrorNotSupported; }
+hipError_t launch_grad_combine(const BwdArgs&, const CombineItem*, int, int, int, hipStream_t) {
+  return hipErrorNotSupported;
+}
 hipError_t launch_fill(const FillArgs&, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_gather(const GatherArgs&, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_scatter(const ScatterArgs&, hipStream_t) { return hipErrorNotSupported; }

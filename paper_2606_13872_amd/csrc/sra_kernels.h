@@ -41,7 +41,11 @@ struct BwdArgs {
   int32_t heads;
   float scale;            // softmax scale
   float scale_log2;
+  float* part_kv;          // slots of split dK/dV items: dK unscaled and dV [256, D]
+  float* part_q;           // slots of split dQ items: dQ unscaled [256, D]
 };
+
+enum class GradKind { kDkv, kDq, kBoth };
 
 struct DeltaArgs {
   const __bf16* o[2];
@@ -95,8 +99,9 @@ struct ScatterArgs {
 hipError_t launch_forward(const FwdArgs& a, int n_items, int head_dim, hipStream_t stream);
 hipError_t launch_forward_combine(const FwdArgs& a, const CombineItem* items, int n, int head_dim, hipStream_t stream);
 hipError_t launch_delta(const DeltaArgs& a, int head_dim, hipStream_t stream);
-hipError_t launch_dq(const BwdArgs& a, int n_items, int head_dim, hipStream_t stream);
-hipError_t launch_dkv(const BwdArgs& a, int n_items, int head_dim, hipStream_t stream);
+hipError_t launch_grad(GradKind kind, const BwdArgs& a, int n_items, int head_dim, hipStream_t stream);
+hipError_t launch_grad_combine(const BwdArgs& a, const CombineItem* items, int n_kv, int n, int head_dim,
+                               hipStream_t stream);
 hipError_t launch_fill(const FillArgs& a, hipStream_t stream);
 hipError_t launch_gather(const GatherArgs& a, hipStream_t stream);
 hipError_t launch_scatter(const ScatterArgs& a, hipStream_t stream);

@@ -20,9 +20,10 @@ def _regs(t):
 
 
 def _scan(text):
-    """(asm MFMAs, hazards, accumulator reads less than 12 wait states behind an asm MFMA)"""
+    """(asm MFMAs, hazards, accumulator reads less than 12 wait states behind the MFMA that wrote it)"""
     count, hazards, early = 0, [], []
-    prev, in_asm, since = [], False, 10 ** 6  # wait states since the last asm MFMA
+    left = False
+    prev, in_asm, now, written = [], False, 0, {}  # wait states so far; when an accumulator was written
     for n, line in enumerate(text.splitlines(), 1):
         t = line.strip()
         if t.startswith(";;#ASMSTART"):
@@ -35,21 +36,27 @@ def _scan(text):
             continue
         if re.match(r"^[.\w$]+:", t):
             prev = []
+            if left:  # nothing falls through to here
+                written.clear()
             continue
         op = t.split()[0]
+        left = op in ("s_branch", "s_endpgm")
         args = [x.strip() for x in t[len(op):].split(";")[0].split(",")]
         if op == "s_nop":
             prev = (prev + [set()] * (int(args[0]) + 1))[-2:]
-            since += int(args[0]) + 1
+            now += int(args[0]) + 1
             continue
-        since += 1
+        now += 1
         if in_asm and op.startswith("v_mfma"):
             count += 1
-            since = 0
+            written.update((r, now) for r in _regs(args[0]))
             use = _regs(args[1]) | _regs(args[2])
             hazards += [(n, t) for w in prev if w & use]
-        if op == "v_accvgpr_read_b32" and since < 12:
+        if op.startswith("v_accvgpr") and len(args) > 1 and any(now - written.get(r, -99) < 12 for r in _regs(args[1])):
             early.append((n, t))
+        if op.startswith("v_accvgpr_") and op != "v_accvgpr_read_b32":
+            for r in _regs(args[0]):
+                written.pop(r, None)
         write = set()
         if op.startswith("v_") and not op.startswith(("v_mfma", "v_cmp")):
             write = _regs(args[0])
@@ -57,7 +64,7 @@ def _scan(text):
     return count, hazards, early
 
 
-@pytest.mark.parametrize("src", ["sra_dq.hip", "sra_dkv.hip"])
+@pytest.mark.parametrize("src", ["sra_grad.hip"])
 def test_assembly_mfma_operands_are_settled(src, tmp_path):
     out = tmp_path / "k.s"
     cmd = [b.hipcc(), *b.HIP_FLAGS, *b.EXTRA_FLAGS.get(src, []), *b.COMMON, "--cuda-device-only", "-S",
