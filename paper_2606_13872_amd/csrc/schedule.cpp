@@ -446,20 +446,24 @@ struct KernelCost {
   double combine;  // the combine launch
 };
 
-// When a launch of these times, longest first, would end on kNumCus compute units.
-double makespan(std::vector<double>& t) {
-  std::sort(t.begin(), t.end(), std::greater<double>());
-  std::priority_queue<double, std::vector<double>, std::greater<double>> cu;
+// When a launch of these times (and how many items take each), longest first, would end on kNumCus
+// compute units. Heads and tiles repeat a few times over, so whole groups of units take whole
+// groups of items: the replay's cost goes with the kinds of items, not with their number (the whole
+// plan of the 480p layer's 5 heads: 4.4 -> 0.48 ms on the host).
+double makespan(std::vector<std::pair<double, int64_t>>& t) {
+  std::sort(t.begin(), t.end(), std::greater<std::pair<double, int64_t>>());
+  std::map<double, int64_t> free_at{{0.0, kNumCus}};  // compute units by the time they are free
   double end = 0;
-  for (double x : t) {
-    double at = 0;
-    if (int(cu.size()) >= kNumCus) {
-      at = cu.top();
-      cu.pop();
+  for (const auto& [x, count] : t)
+    for (int64_t left = count; left > 0;) {
+      const auto first = free_at.begin();
+      const double done = first->first + x;
+      const int64_t n = std::min(left, first->second);
+      left -= n;
+      if ((first->second -= n) == 0) free_at.erase(first);
+      free_at[done] += n;
+      end = std::max(end, done);
     }
-    cu.push(at + x);
-    end = std::max(end, at + x);
-  }
   return end;
 }
 
@@ -482,48 +486,59 @@ struct Timed {
 // items of a head in step on an XCD is worth more than the last round.
 std::vector<int32_t> choose_split(const std::vector<Timed>& v, int64_t max_bytes, double* end) {
   const size_t n = v.size();
-  std::vector<int32_t> best(n, 1), k(n);
+  std::vector<int32_t> best(n, 1);
   *end = 0;
   if (n == 0) return best;
-  double total = 0;
-  for (const Timed& x : v) total += x.time();
   if (n > size_t(kSplitRounds * kNumCus)) {
+    double total = 0;
+    for (const Timed& x : v) total += x.time();
     *end = total / kNumCus + 0.5 * v[0].time();
     return best;
   }
-  std::vector<double> t;
-  auto eval = [&](const std::vector<int32_t>& parts) {
-    t.clear();
-    double combine = 0;
-    for (size_t i = 0; i < n; ++i) {
-      const KernelCost& c = *v[i].c;
-      if (parts[i] > 1) combine = std::max(combine, c.combine);
-      for (int32_t j = 0; j < parts[i]; ++j)
-        t.push_back(double(v[i].steps) / parts[i] * c.step + c.item + (parts[i] > 1 ? c.piece : 0));
-    }
-    return makespan(t) + combine;
-  };
-  *end = eval(best);
-  const double whole = *end, longest = v[0].steps * v[0].c->step;
+  const double longest = v[0].steps * v[0].c->step;
   size_t n_long = 0;
   while (n_long < n && 2 * v[n_long].time() >= v[0].time()) ++n_long;
   const size_t rounds = n_long / kNumCus * kNumCus;
+  std::vector<size_t> at;  // where runs of like items begin, and the end; also the first of the last round
+  for (size_t i = 0; i < n; ++i)
+    if (i == 0 || i == rounds || v[i].steps != v[i - 1].steps || v[i].c != v[i - 1].c) at.push_back(i);
+  at.push_back(n);
+  const size_t m = at.size() - 1;
+  std::vector<int32_t> chosen(m, 1), k(m, 1), last;
+  std::vector<std::pair<double, int64_t>> t;
+  auto eval = [&](const std::vector<int32_t>& parts) {
+    t.clear();
+    double combine = 0;
+    for (size_t r = 0; r < m; ++r) {
+      const Timed& x = v[at[r]];
+      const KernelCost& c = *x.c;
+      if (parts[r] > 1) combine = std::max(combine, c.combine);
+      t.push_back({double(x.steps) / parts[r] * c.step + c.item + (parts[r] > 1 ? c.piece : 0),
+                   int64_t(at[r + 1] - at[r]) * parts[r]});
+    }
+    return makespan(t) + combine;
+  };
+  *end = eval(chosen);
+  const double whole = *end;
   for (int32_t parts = 2; parts <= 24; ++parts) {
     for (int tail = 0; tail < (rounds > 0 ? 2 : 1); ++tail) {
       int64_t bytes = 0;
-      for (size_t i = 0; i < n; ++i) {
-        const double piece = std::max(2.0 * v[i].c->step, longest / parts);  // two steps at least
-        k[i] = i < (tail ? rounds : 0) ? 1 : std::max<int32_t>(1, int32_t(std::ceil(v[i].steps * v[i].c->step / piece - 1e-9)));
-        if (k[i] > 1) bytes += k[i] * v[i].bytes;
+      for (size_t r = 0; r < m; ++r) {
+        const Timed& x = v[at[r]];
+        const double piece = std::max(2.0 * x.c->step, longest / parts);  // two steps at least
+        k[r] = at[r] < (tail ? rounds : 0) ? 1 : std::max<int32_t>(1, int32_t(std::ceil(x.steps * x.c->step / piece - 1e-9)));
+        if (k[r] > 1) bytes += k[r] * x.bytes * int64_t(at[r + 1] - at[r]);
       }
-      if (bytes == 0 || bytes > max_bytes) continue;
+      if (bytes == 0 || bytes > max_bytes || k == last) continue;  // pieces no longer get shorter
+      last = k;
       const double e = eval(k);
       if (e < *end && e < 0.97 * whole) {
         *end = e;
-        best = k;
+        chosen = k;
       }
     }
   }
+  for (size_t r = 0; r < m; ++r) std::fill(best.begin() + at[r], best.begin() + at[r + 1], chosen[r]);
   return best;
 }
 
@@ -597,9 +612,11 @@ std::vector<int32_t> sort_steps(CostedItems& v, const Schedule& s) {
   std::stable_sort(v.begin(), v.end(), [](const auto& a, const auto& b) { return a.first > b.first; });
   std::map<std::pair<int32_t, int32_t>, int32_t> known;
   std::vector<int32_t> steps;
-  for (const auto& e : v) {
+  steps.reserve(v.size());
+  auto it = known.end();
+  for (const auto& e : v) {  // items of one span list mostly follow one another
     const auto key = std::make_pair(e.second.span_off, e.second.span_cnt);
-    auto it = known.find(key);
+    if (it == known.end() || it->first != key) it = known.find(key);
     if (it == known.end()) {
       int32_t n = 0;
       for (int32_t i = 0; i < key.second; ++i) n += span_steps(s.spans[size_t(key.first) + i]);
@@ -622,35 +639,40 @@ void launch_forward_schedule(const Layout& L, int64_t max_bytes, Schedule* out) 
   Layout all = L;
   all.gen_only = false;
   double best = 0;
+  CostedItems v;
+  std::vector<int32_t> parts;
   for (int tile : {kFwdQueryTile, fwd_large_tile(L.head_dim)}) {
     const bool large = tile != kFwdQueryTile;
     const KernelCost c{!large ? 1.0 : L.head_dim == 128 ? 1.36 : 1.72, 3.0, large ? 3.0 : 2.0, 4.0};
     Schedule s;
-    CostedItems v = query_major_items(all, tile, kFwdKeyStep, &s);
-    const std::vector<int32_t> steps = sort_steps(v, s);
+    CostedItems items = query_major_items(all, tile, kFwdKeyStep, &s);
+    const std::vector<int32_t> steps = sort_steps(items, s);
     std::vector<Timed> timed;
+    timed.reserve(steps.size());
     for (int32_t n : steps) timed.push_back({n, &c, slot_bytes(tile, L.head_dim, 1, 2)});
     double end;
-    std::vector<int32_t> parts = choose_split(timed, max_bytes, &end);
+    std::vector<int32_t> k = choose_split(timed, max_bytes, &end);
     if (large && !(end < 0.99 * best)) continue;
     best = end;
-    if (L.gen_only) {  // the gen rows' items, as in the call of all rows
-      size_t n = 0;
-      for (size_t i = 0; i < v.size(); ++i)
-        if (v[i].second.stream == 0) {
-          v[n] = v[i];
-          parts[n++] = parts[i];
-        }
-      v.resize(n);
-      parts.resize(n);
-    }
-    if (std::any_of(parts.begin(), parts.end(), [](int32_t k) { return k > 1; })) {
-      split_items(v, parts, false, &s);
-    } else {
-      finish_whole(v, L, kFwdKeyStep, false, &s);
-    }
     s.tile = tile;
+    v.swap(items);
+    parts.swap(k);
     *out = std::move(s);
+  }
+  if (L.gen_only) {  // the gen rows' items, as in the call of all rows
+    size_t n = 0;
+    for (size_t i = 0; i < v.size(); ++i)
+      if (v[i].second.stream == 0) {
+        v[n] = v[i];
+        parts[n++] = parts[i];
+      }
+    v.resize(n);
+    parts.resize(n);
+  }
+  if (std::any_of(parts.begin(), parts.end(), [](int32_t k) { return k > 1; })) {
+    split_items(v, parts, false, out);
+  } else {
+    finish_whole(v, L, kFwdKeyStep, false, out);
   }
 }
 

@@ -11,12 +11,13 @@ namespace sra {
 constexpr int kFwdQueryTile = 256;
 constexpr int kFwdKeyStep = 64;
 constexpr int fwd_large_tile(int head_dim) { return head_dim == 128 ? 384 : 512; }
-// dQ kernel of the backward: 256-row query tiles as in the forward, held by 4 wave64s (one per
-// SIMD, 64 query rows each); keys stream through LDS 32 at a time.
+// dQ kernel of the backward: 256-row query tiles, held by 4 wave64s (one per
+// SIMD, 64 query rows each); keys stream through LDS 64 at a time. kDqKeyStep and kDkvQueryStep
+// are the steps in which the scheduler counts a long launch's phases.
 constexpr int kDqQueryTile = 256;
 constexpr int kDqKeyStep = 32;
 // dK/dV kernel of the backward: 4 wave64s (one per SIMD) x 64 keys = 256 keys per work item;
-// queries stream through LDS 32 at a time.
+// queries stream through LDS 64 at a time.
 constexpr int kDkvKeyTile = 256;
 constexpr int kDkvQueryStep = 32;
 
