@@ -135,7 +135,9 @@ __device__ __forceinline__ void rescale_half(FwdState<D, NQ>& st, HalfS<NQ>& s, 
 #pragma unroll
       for (int db = 0; db < D / 16; ++db) st.o[qb][db] *= alpha;
     }
-    const float nm = -st.m[qb];
+    // A row whose scores so far are all -inf (keys masked by an infinite head dim) keeps P = 0, wherever
+    // its work item or piece begins.
+    const float nm = st.m[qb] == -INFINITY ? 0.f : -st.m[qb];
     float acc = 0.f;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {

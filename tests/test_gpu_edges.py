@@ -57,3 +57,23 @@ def test_long_streams_repeat_bitwise(d, packed):
         do = torch.cat([x["do_gen"][:, h], x["do_ref"][:, h]]).double().sum(0)
         assert float((dv - do).norm() / do.norm()) < 0.04
     assert np.isfinite(float(first["dq_gen"].float().sum()))
+
+
+@pytest.mark.parametrize("masked", [(0, 500), (130, 700)])
+@pytest.mark.parametrize("heads,d", [(3, 128), (1, 64), (24, 64)])
+def test_keys_masked_by_an_infinite_head_dim(heads, d, masked):
+    """Keys whose first head dim is -inf (the queries' is 1) have scores of -inf: weight 0, also where a
+    work item or a piece of a split one begins with them."""
+    s = SampleGeom(2, 20, 20, 3, 13, 11)
+    print(f"[masked keys] heads {heads} d {d} masked {masked}", flush=True)
+    x = make_inputs([s], heads, d, 70, device="cuda")
+    x["q_gen"][:, :, 0] = 1
+    x["k_gen"][masked[0]:masked[1], :, 0] = float("-inf")
+    o, _, lse, _ = sra.forward(*[x[n] for n in ("q_gen", "k_gen", "v_gen", "q_ref", "k_ref", "v_ref")], [s])
+    k, v = (torch.cat([x[n + "_gen"], x[n + "_ref"]]).double().cpu() for n in "kv")
+    q = x["q_gen"].double().cpu()
+    for h in range(heads):
+        sc = (q[:, h] @ k[:, h].T) / d ** 0.5
+        assert float((lse[h].double().cpu() - torch.logsumexp(sc, -1)).abs().max()) < 1e-3
+        want = torch.softmax(sc, -1) @ v[:, h]
+        assert float((o[:, h].double().cpu() - want).norm() / want.norm()) < 1e-2  # bf16 P and O: 2.5e-3
