@@ -479,12 +479,21 @@ struct Timed {
   double time() const { return steps * c->step + c->item; }
 };
 
+// Microseconds that writing and reading these partial results adds to a launch: little while the
+// caches hold them (12 heads of 220 + 330 tokens, 49 MB: the split backward 60 -> 50 us), up to
+// 1 TB/s beyond (5 heads of 3,060 + 2,142 tokens, 80 MB: 40 us over the end replayed without them).
+double partials_us(int64_t bytes) {
+  constexpr int64_t kCached = int64_t(64) << 20;
+  return double(bytes) / 10e6 + double(std::max<int64_t>(0, bytes - kCached)) / 1e6;
+}
+
 // Pieces per item (same order as `v`, which is longest first) that end the launch earliest, or
 // all ones; *end is that time. Tried: every item longer than a part of the longest cut to such
 // parts, and the same for only those items of the long ones that a last, partial round of the
 // compute units would hold. Not for launches of over kSplitRounds rounds: there the order that keeps
-// items of a head in step on an XCD is worth more than the last round.
-std::vector<int32_t> choose_split(const std::vector<Timed>& v, int64_t max_bytes, double* end) {
+// items of a head in step on an XCD is worth more than the last round. unit_us: one unit of the
+// times in microseconds.
+std::vector<int32_t> choose_split(const std::vector<Timed>& v, int64_t max_bytes, double unit_us, double* end) {
   const size_t n = v.size();
   std::vector<int32_t> best(n, 1);
   *end = 0;
@@ -506,7 +515,7 @@ std::vector<int32_t> choose_split(const std::vector<Timed>& v, int64_t max_bytes
   const size_t m = at.size() - 1;
   std::vector<int32_t> chosen(m, 1), k(m, 1), last;
   std::vector<std::pair<double, int64_t>> t;
-  auto eval = [&](const std::vector<int32_t>& parts) {
+  auto eval = [&](const std::vector<int32_t>& parts, int64_t bytes) {
     t.clear();
     double combine = 0;
     for (size_t r = 0; r < m; ++r) {
@@ -516,9 +525,9 @@ std::vector<int32_t> choose_split(const std::vector<Timed>& v, int64_t max_bytes
       t.push_back({double(x.steps) / parts[r] * c.step + c.item + (parts[r] > 1 ? c.piece : 0),
                    int64_t(at[r + 1] - at[r]) * parts[r]});
     }
-    return makespan(t) + combine;
+    return makespan(t) + combine + partials_us(bytes) / unit_us;
   };
-  *end = eval(chosen);
+  *end = eval(chosen, 0);
   const double whole = *end;
   for (int32_t parts = 2; parts <= 24; ++parts) {
     for (int tail = 0; tail < (rounds > 0 ? 2 : 1); ++tail) {
@@ -531,7 +540,7 @@ std::vector<int32_t> choose_split(const std::vector<Timed>& v, int64_t max_bytes
       }
       if (bytes == 0 || bytes > max_bytes || k == last) continue;  // pieces no longer get shorter
       last = k;
-      const double e = eval(k);
+      const double e = eval(k, bytes);
       if (e < *end && e < 0.97 * whole) {
         *end = e;
         chosen = k;
@@ -632,6 +641,8 @@ std::vector<int32_t> sort_steps(CostedItems& v, const Schedule& s) {
 constexpr int64_t kTableBytes = int64_t(4) << 20;
 constexpr int64_t kFwdPartialBytes = int64_t(SRA_NOALLOC_WORKSPACE_MAX) - kTableBytes;
 
+constexpr double kFwdUnitUs = 1.5;  // a 64-key step of 256 rows at d = 128 (1.1 at d = 64)
+
 // The forward's launch: rows per item and splits by the replayed end. A step of the large tile
 // holds 1.5 (d = 128) or 2 (d = 64) times the rows and takes 1.36 or 1.72 times as long (480p, 40
 // heads: 25.5 -> 23.7 ms; 480p, d = 64, 16 heads: 8.35 -> 7.24 ms). max_bytes: of partial results.
@@ -643,7 +654,7 @@ void launch_forward_schedule(const Layout& L, int64_t max_bytes, Schedule* out) 
   std::vector<int32_t> parts;
   for (int tile : {kFwdQueryTile, fwd_large_tile(L.head_dim)}) {
     const bool large = tile != kFwdQueryTile;
-    const KernelCost c{!large ? 1.0 : L.head_dim == 128 ? 1.36 : 1.72, 3.0, large ? 3.0 : 2.0, 4.0};
+    const KernelCost c{!large ? 1.0 : L.head_dim == 128 ? 1.36 : 1.72, 3.0, large ? 3.0 : 2.0, L.head_dim == 128 ? 4.0 : 7.0};
     Schedule s;
     CostedItems items = query_major_items(all, tile, kFwdKeyStep, &s);
     const std::vector<int32_t> steps = sort_steps(items, s);
@@ -651,7 +662,7 @@ void launch_forward_schedule(const Layout& L, int64_t max_bytes, Schedule* out) 
     timed.reserve(steps.size());
     for (int32_t n : steps) timed.push_back({n, &c, slot_bytes(tile, L.head_dim, 1, 2)});
     double end;
-    std::vector<int32_t> k = choose_split(timed, max_bytes, &end);
+    std::vector<int32_t> k = choose_split(timed, max_bytes, kFwdUnitUs, &end);
     if (large && !(end < 0.99 * best)) continue;
     best = end;
     s.tile = tile;
@@ -676,11 +687,14 @@ void launch_forward_schedule(const Layout& L, int64_t max_bytes, Schedule* out) 
   }
 }
 
-// The backward's launches. Times in units of 0.75 us (a dQ step takes 2.25 us, a dK/dV step 3.0, a
-// launch and its first tile about 6): up to kSplitRounds rounds of items run as one launch,
-// split where that ends earlier; longer launches run kind by kind, each in its own order.
+// The backward's launches. Times in units of 0.75 us: a dQ step takes 2.25 us and a dK/dV step 3.0
+// at d = 128 (1.4 and 1.85 at d = 64), a launch and its first tile about 6. Up to kSplitRounds rounds
+// of items run as one launch, split where that ends earlier; longer launches run kind by kind,
+// each in its own order.
 constexpr int64_t kBwdPartialBytes = int64_t(256) << 20;
-const KernelCost kDkvCost{4.0, 8.0, 8.0, 8.0}, kDqCost{3.0, 8.0, 5.0, 8.0};
+constexpr double kBwdUnitUs = 0.75;
+const KernelCost kDkvCosts[2] = {{2.4, 8.0, 8.0, 8.0}, {4.0, 8.0, 8.0, 8.0}};  // d = 64, 128
+const KernelCost kDqCosts[2] = {{1.8, 8.0, 5.0, 8.0}, {3.0, 8.0, 5.0, 8.0}};
 
 void launch_backward_schedules(const Layout& L, Plan* plan) {
   // Whether and how items are split is settled for the call of all rows, so that the gradients of
@@ -707,16 +721,17 @@ void launch_backward_schedules(const Layout& L, Plan* plan) {
     return;
   }
   // entry i < vk.size(): key item i, else query item i - vk.size()
+  const KernelCost &dkv_cost = kDkvCosts[L.head_dim == 128], &dq_cost = kDqCosts[L.head_dim == 128];
   const std::vector<int32_t> sk = sort_steps(vk, dkv), sq = sort_steps(vq, dq);
   std::vector<Timed> timed, sorted;
-  for (int32_t n : sk) timed.push_back({n, &kDkvCost, slot_bytes(kDkvKeyTile, L.head_dim, 2, 0)});
-  for (int32_t n : sq) timed.push_back({n, &kDqCost, slot_bytes(kDqQueryTile, L.head_dim, 1, 0)});
+  for (int32_t n : sk) timed.push_back({n, &dkv_cost, slot_bytes(kDkvKeyTile, L.head_dim, 2, 0)});
+  for (int32_t n : sq) timed.push_back({n, &dq_cost, slot_bytes(kDqQueryTile, L.head_dim, 1, 0)});
   std::vector<int32_t> order(timed.size());
   std::iota(order.begin(), order.end(), 0);
   std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return timed[a].time() > timed[b].time(); });
   for (int32_t i : order) sorted.push_back(timed[i]);
   double end;
-  const std::vector<int32_t> k = choose_split(sorted, kBwdPartialBytes, &end);
+  const std::vector<int32_t> k = choose_split(sorted, kBwdPartialBytes, kBwdUnitUs, &end);
   std::vector<int32_t> pk(vk.size()), pq(vq.size());
   for (size_t i = 0; i < order.size(); ++i) {
     if (size_t(order[i]) < vk.size()) pk[order[i]] = k[i];
@@ -753,8 +768,8 @@ void launch_backward_schedules(const Layout& L, Plan* plan) {
     }
     g.combine.insert(g.combine.end(), s.combine.begin(), s.combine.end());
   };
-  add(dkv, kDkvCost, 0);
-  add(dq, kDqCost, 2);
+  add(dkv, dkv_cost, 0);
+  add(dq, dq_cost, 2);
   std::stable_sort(all.begin(), all.end(), [](const auto& a, const auto& b) { return a.first > b.first; });
   for (auto& e : all) g.items.push_back(e.second);
   g.real_items = int64_t(g.items.size());
