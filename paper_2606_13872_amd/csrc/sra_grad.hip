@@ -3,7 +3,8 @@
 // kinds together (sra_grad_kernel): one launch less, and the one kind fills the compute units that
 // the other's last round leaves idle. A long launch runs the two kernels one after the other: each
 // kind's items are then ordered so that those resident on an XCD share rows through its L2, and a
-// last round is worth little.
+// last round is worth little. One launch and split items: 480p, 5 heads 11.8 -> 10.7 ms; 8 heads of
+// 1,280 + 1,024 tokens, d = 64, 111 -> 47 us.
 #include "sra_dkv.h"
 #include "sra_dq.h"
 
@@ -41,7 +42,8 @@ sra_grad_kernel(BwdArgs a) {
 }
 
 // Sums of the split items' pieces, in piece order: items [0, n_kv) dK and dV, the others dQ.
-// D / 4 threads per row.
+// D / 4 threads per row. Bound by reading the partial sums; a few microseconds behind a launch that ends
+// earlier by more (the scheduler's replay).
 template <int D>
 __global__ void __launch_bounds__(kThreads) sra_grad_combine_kernel(BwdArgs a, const CombineItem* items, int n_kv) {
   constexpr int TPR = D / 4, RPB = kThreads / TPR;
