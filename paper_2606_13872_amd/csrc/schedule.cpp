@@ -551,21 +551,9 @@ std::vector<int32_t> choose_split(const std::vector<Timed>& v, int64_t max_bytes
   return best;
 }
 
-// Steps of an item: of its gen spans (which come first) and of the others.
-std::pair<int32_t, int32_t> item_steps(const WorkItem& w, const Schedule& s) {
-  std::pair<int32_t, int32_t> n{0, 0};
-  for (int32_t i = 0; i < w.span_cnt; ++i) {
-    const Span& x = s.spans[size_t(w.span_off) + i];
-    (x.stream == 0 ? n.first : n.second) += span_steps(x);
-  }
-  return n;
-}
-
-// Replaces the items of v (longest first, with their spans in s) by their pieces, into s: parts[i] of
-// the item's steps; or with `own_ref` of the steps of its gen spans alone, its ref spans going with
-// the last of them, or as pieces of their own where they are longer than such a piece. (A key
-// tile's gen queries are then cut the same way whether or not the ref queries are computed.)
-void split_items(const CostedItems& v, const std::vector<int32_t>& parts, bool own_ref, Schedule* s) {
+// Replaces the items of v (longest first, with their spans in s) by their pieces, into s: parts[i]
+// pieces of like numbers of steps each, at most as many as the item has steps.
+void split_items(const CostedItems& v, const std::vector<int32_t>& parts, Schedule* s) {
   std::vector<Span> spans;
   std::map<std::pair<int32_t, std::pair<int32_t, int32_t>>, std::pair<int32_t, int32_t>> made;
   std::vector<std::pair<int32_t, WorkItem>> out;
@@ -584,22 +572,15 @@ void split_items(const CostedItems& v, const std::vector<int32_t>& parts, bool o
     }
     return made[key] = {off, int32_t(spans.size()) - off};
   };
-  std::vector<int32_t> ends;
   for (size_t i = 0; i < v.size(); ++i) {
     const WorkItem& w = v[i].second;
-    const auto n = item_steps(w, *s);
-    const int32_t all = n.first + n.second, body = own_ref && n.first > 0 ? n.first : all;
-    ends.clear();
-    for (int32_t j = 1; j <= parts[i]; ++j) ends.push_back(int32_t(int64_t(body) * j / parts[i]));
-    if (body < all) {
-      const int32_t piece = (body + parts[i] - 1) / parts[i], extra = parts[i] > 1 ? (all - body) / piece : 0;
-      if (extra == 0) ends.back() = all;
-      for (int32_t j = 1; j <= extra; ++j) ends.push_back(body + int32_t(int64_t(all - body) * j / extra));
-    }
-    const int32_t k = int32_t(ends.size());
+    int32_t steps = 0;
+    for (int32_t j = 0; j < w.span_cnt; ++j) steps += span_steps(s->spans[size_t(w.span_off) + j]);
+    const int32_t k = parts[i];
     if (k > 1) s->combine.push_back({w.stream, w.head, w.start, w.len, s->slots, k, {0, 0}});
     int32_t from = 0;
-    for (int32_t to : ends) {
+    for (int32_t j = 1; j <= k; ++j) {
+      const int32_t to = int32_t(int64_t(steps) * j / k);
       WorkItem x = w;
       const auto c = cut(w, from, to);
       x.span_off = c.first;
@@ -614,6 +595,46 @@ void split_items(const CostedItems& v, const std::vector<int32_t>& parts, bool o
   for (auto& e : out) s->items.push_back(e.second);
   s->real_items = int64_t(s->items.size());
   s->spans.swap(spans);
+}
+
+// Leaves of split_items' launch of all rows what the call of the gen queries alone needs: query
+// items and pieces of the gen rows; of key items and pieces (key_major) the gen queries' spans,
+// which come first in every list. Slots are numbered anew, and an item left with one piece is whole:
+// what is dropped would only have added zeros (a reference query whose output has no gradient).
+void keep_gen_queries(bool key_major, Schedule* s) {
+  std::vector<WorkItem> items;
+  std::vector<Span> spans;
+  std::map<std::pair<int32_t, int32_t>, int32_t> made;  // (span list's offset, spans kept) -> new offset
+  std::vector<int32_t> slot(size_t(s->slots) + 1, 0);   // old slot -> 1 if kept, then the new slot
+  for (WorkItem w : s->items) {
+    const Span* l = &s->spans[size_t(w.span_off)];
+    if (key_major) {
+      int32_t n = 0;
+      while (n < w.span_cnt && l[n].stream == 0) ++n;
+      w.span_cnt = n;
+    }
+    if (key_major ? w.span_cnt == 0 : w.stream != 0) continue;
+    const auto at = made.emplace(std::make_pair(w.span_off, w.span_cnt), int32_t(spans.size()));
+    if (at.second) spans.insert(spans.end(), l, l + w.span_cnt);
+    w.span_off = at.first->second;
+    if (w.slot) slot[size_t(w.slot)] = 1;
+    items.push_back(w);
+  }
+  std::vector<CombineItem> combine;
+  s->slots = 0;
+  for (CombineItem c : s->combine) {
+    const auto first = slot.begin() + c.slot0 + 1, last = first + c.n;
+    c.slot0 = s->slots;
+    c.n = int32_t(std::count(first, last, 1));
+    for (auto x = first; x != last; ++x)
+      if (*x) *x = c.n > 1 ? ++s->slots : 0;
+    if (c.n > 1) combine.push_back(c);
+  }
+  for (WorkItem& w : items) w.slot = slot[size_t(w.slot)];
+  s->items.swap(items);
+  s->spans.swap(spans);
+  s->combine.swap(combine);
+  s->real_items = int64_t(s->items.size());
 }
 
 // Sorts v longest first and returns the items' steps.
@@ -681,7 +702,7 @@ void launch_forward_schedule(const Layout& L, int64_t max_bytes, Schedule* out) 
     parts.resize(n);
   }
   if (std::any_of(parts.begin(), parts.end(), [](int32_t k) { return k > 1; })) {
-    split_items(v, parts, false, out);
+    split_items(v, parts, out);
   } else {
     finish_whole(v, L, kFwdKeyStep, false, out);
   }
@@ -737,23 +758,12 @@ void launch_backward_schedules(const Layout& L, Plan* plan) {
     if (size_t(order[i]) < vk.size()) pk[order[i]] = k[i];
     else pq[order[i] - vk.size()] = k[i];
   }
+  split_items(vk, pk, &dkv);
+  split_items(vq, pq, &dq);
   if (L.gen_only) {
-    size_t n = 0;
-    for (size_t i = 0; i < vq.size(); ++i)
-      if (vq[i].second.stream == 0) {
-        vq[n] = vq[i];
-        pq[n++] = pq[i];
-      }
-    vq.resize(n);
-    pq.resize(n);
-    for (auto& e : vk) {  // the gen queries' spans come first
-      int32_t m = 0;
-      while (m < e.second.span_cnt && dkv.spans[size_t(e.second.span_off) + m].stream == 0) ++m;
-      e.second.span_cnt = m;
-    }
+    keep_gen_queries(true, &dkv);
+    keep_gen_queries(false, &dq);
   }
-  split_items(vk, pk, true, &dkv);
-  split_items(vq, pq, false, &dq);
   Schedule& g = plan->grad;
   std::vector<std::pair<double, WorkItem>> all;
   auto add = [&](const Schedule& s, const KernelCost& c, int32_t mark) {

@@ -815,6 +815,7 @@ static sra_status expand(const Layout& L, const Plan& P, const Schedule& S, bool
   };
   for (const WorkItem& w : S.items) {
     if (w.stream < 0 || w.head != head || w.sample != sample) continue;
+    if (w.span_cnt < 1) return fail(SRA_ERR_INTERNAL, "schedule holds an item without spans");
     for (int32_t si = 0; si < w.span_cnt; ++si) {
       const Span& sp = S.spans[w.span_off + si];
       // a key-major span may reach only the item's keys [lo, hi)

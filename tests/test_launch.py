@@ -61,3 +61,52 @@ def test_partial_results_leave_the_allocation_free_forward_its_calls(heads, dim)
         if any(s.ref_token_valid is not None for s in samples):
             continue
         assert sra.Problem(samples, heads, dim).workspace_size(False) <= sra.noalloc_workspace_max()
+
+
+PARTIAL_BYTES = 256 << 20  # a backward's partial results
+LONG_GROUPS = {
+    "1x24x24|9x52x30": ([SampleGeom(1, 24, 24, 9, 52, 30, group_frames=9)], 1),
+    "1x16x16|4x60x60": ([SampleGeom(1, 16, 16, 4, 60, 60, group_frames=4)], 2),
+    "4x17x1|16x60x49": ([SampleGeom(4, 17, 1, 16, 60, 49, group_frames=8)], 1),
+    "two": ([SampleGeom(1, 13, 21, 19, 23, 7, group_frames=9), SampleGeom(1, 5, 37, 21, 54, 51, group_frames=12)], 1),
+    "1x8x8|9x45x80": ([SampleGeom(1, 8, 8, 9, 45, 80, group_frames=9)], 1),
+    "mixed": ([SampleGeom(1, 8, 8, 9, 30, 52, group_frames=9), SampleGeom(5, 30, 52, 9, 30, 52, group_frames=9)], 1),
+}
+
+
+def _random_long_group(rng):
+    def sample():
+        rf = int(rng.integers(1, 22))
+        return SampleGeom(int(rng.integers(1, 5)), int(rng.integers(1, 25)), int(rng.integers(1, 25)), rf,
+                          int(rng.integers(1, 61)), int(rng.integers(1, 61)), group_frames=int(rng.integers(1, rf + 1)))
+    return [sample() for _ in range(int(rng.integers(1, 4)))]
+
+
+def test_backward_partial_results_stay_within_their_bound():
+    """Few gen rows and groups as long as the clip: the pieces of a key tile's gen and reference queries
+    are counted as they are cut. Beside the partial results the workspace holds the tables (under
+    4 MiB here) and two values per row and head."""
+    rng = np.random.default_rng(17)
+    calls = list(LONG_GROUPS.values()) + [(_random_long_group(rng), int(rng.integers(1, 4))) for _ in range(300)]
+    split = 0
+    for samples, heads in calls:
+        for flags in (0, sra.FLAG_GEN_QUERIES_ONLY):
+            rows = sum(s.n_gen + s.n_ref for s in samples)
+            need = sra.Problem(samples, heads, 128, flags=flags).workspace_size(True)
+            assert need <= PARTIAL_BYTES + (4 << 20) + 8 * heads * rows, (samples, heads, flags)
+        split += sra.launch_info(samples, sra.SCHED_BWD_DKDV, heads=heads)[2] > 0
+    assert split >= 100  # the calls are ones that are split
+
+
+@pytest.mark.parametrize("flags", [0, sra.FLAG_GEN_QUERIES_ONLY])
+@pytest.mark.parametrize("gen,ref", [((1, 8, 8), (4, 16, 33)), ((1, 3, 11), (6, 11, 17)), ((2, 9, 13), (3, 29, 21))])
+def test_few_gen_rows_and_long_groups_launch_no_empty_pieces(gen, ref, flags):
+    """The expansion refuses an item without spans, so each piece has some; and covers the mask."""
+    samples = [SampleGeom(*gen, *ref, group_frames=ref[0])]
+    want = oracle.visibility_mask(samples[0]).astype(np.uint8)
+    if flags:
+        want[samples[0].n_gen:] = 0
+    for which in SCHEDS:
+        got = sra.launch_mask(samples, which, 0, 0, heads=1, flags=flags)
+        assert np.array_equal(got, want), which
+    assert sra.launch_info(samples, sra.SCHED_BWD_DKDV, heads=1)[2] > 0
