@@ -213,7 +213,8 @@ sra_status sra_launch_info(const sra_problem* p, int which, int64_t* n_items, in
                            int64_t* split_items);
 
 /* sra_schedule_mask of what a call launches, for head `head`: the pieces of a split item cover
- * its pairs once between them, so the matrix is again exactly the 0/1 visibility mask. */
+ * its pairs once between them, so the matrix is again exactly the 0/1 visibility mask. Fails with
+ * SRA_ERR_INTERNAL where pieces and the slots of their partial results do not match. */
 sra_status sra_launch_mask(const sra_problem* p, int which, int32_t sample, int32_t head,
                            uint8_t* out);
 
@@ -236,6 +237,14 @@ sra_status sra_launch_mask(const sra_problem* p, int which, int32_t sample, int3
  * of that stream. */
 sra_status sra_schedule_export(const sra_problem* p, int which, int32_t* items,
                                int64_t items_capacity, int32_t* spans, int64_t spans_capacity);
+
+/* sra_schedule_export of what a call launches for schedule `which` (the tiles realising §1, §2.1 and
+ * §4.3, larger or cut as sra_launch_info says). items[8*i + 7] is 0, or k for the piece whose partial
+ * results go to slot k - 1. Where a backward runs as one launch, the dQ and dK/dV schedules list
+ * their items of it and share its span table. n_items and n_spans (either may be NULL) receive the
+ * tables' sizes, padding items included. Host only. */
+sra_status sra_launch_export(const sra_problem* p, int which, int32_t* items, int64_t items_capacity,
+                             int32_t* spans, int64_t spans_capacity, int64_t* n_items, int64_t* n_spans);
 
 /* ---- per-kernel timing (tracing hook; library infrastructure, no passage of the paper) --- */
 

@@ -784,8 +784,11 @@ void launch_backward_schedules(const Layout& L, Plan* plan) {
   for (auto& e : all) g.items.push_back(e.second);
   g.real_items = int64_t(g.items.size());
   plan->grad_joint = true;
-  plan->dq = std::move(dq);
-  plan->dkv = std::move(dkv);
+  plan->grad_kv_combine = int32_t(dkv.combine.size());
+  for (auto [from, to] : {std::make_pair(&dq, &plan->dq), std::make_pair(&dkv, &plan->dkv)}) {
+    to->tile = from->tile;
+    to->slots = from->slots;
+  }
 }
 
 }  // namespace

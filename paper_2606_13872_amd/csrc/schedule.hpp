@@ -57,9 +57,10 @@ struct Plan {
   bool compacted = false;          // the schedules index the compacted reference stream
   Layout exec;                     // the layout the schedules index (layout, or its compaction)
   Schedule fwd, dq, dkv;           // as launched: tile sizes chosen, long items split (build_plan)
-  bool grad_joint = false;         // dK/dV and dQ items run in one launch:
-  Schedule grad;                   // those (bit 1 of an item's stream marks a dQ item); no spans or
-                                   // items in dq and dkv are uploaded then
+  bool grad_joint = false;         // dK/dV and dQ items run in one launch: grad; dq and dkv then
+                                   // hold only their tiles and slots
+  Schedule grad;                   // bit 1 of an item's stream marks a dQ item
+  int32_t grad_kv_combine = 0;     // grad.combine: the split dK/dV items, then the dQ ones
   std::vector<FillRange> fill;     // invalid reference rows of exec (none when compacted)
   std::vector<int32_t> ref_gather;   // compacted: packed ref row of each compacted row
   std::vector<int32_t> ref_scatter;  // compacted: compacted row of each packed ref row, or -1

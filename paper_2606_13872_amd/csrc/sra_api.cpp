@@ -693,7 +693,7 @@ sra_status sra_backward(const sra_problem* p, const void* q_gen, const void* k_g
       const hipError_t x = launch_grad(GradKind::kBoth, a, int(P.grad.items.size()), L.head_dim, s);
       if (x != hipSuccess) return x;
       return launch_grad_combine(a, reinterpret_cast<const CombineItem*>(ws + cp->bwd.offsets[7]),
-                                 int(P.dkv.combine.size()), int(P.grad.combine.size()), L.head_dim, s);
+                                 P.grad_kv_combine, int(P.grad.combine.size()), L.head_dim, s);
     });
     if (e != hipSuccess) return hip_fail(e, "gradient launch");
   } else {
@@ -782,6 +782,49 @@ static const Schedule* pick(const Plan& P, int which) {
   }
 }
 
+// Schedule `which` as a call uploads it: where both kinds of gradient items run as one launch, its
+// part of that launch's tables.
+static bool launched(const Plan& P, int which, Schedule* out) {
+  const Schedule* S = pick(P, which);
+  if (!S) return false;
+  *out = *S;
+  if (!P.grad_joint || which == SRA_SCHED_FORWARD) return true;
+  const bool dq = which == SRA_SCHED_BWD_DQ;
+  out->items.clear();
+  for (WorkItem w : P.grad.items) {
+    if (((w.stream & 2) != 0) != dq) continue;
+    w.stream &= 1;
+    out->items.push_back(w);
+  }
+  out->real_items = int64_t(out->items.size());
+  out->spans = P.grad.spans;
+  const auto dq0 = P.grad.combine.begin() + P.grad_kv_combine;
+  if (dq) out->combine.assign(dq0, P.grad.combine.end());
+  else out->combine.assign(P.grad.combine.begin(), dq0);
+  return true;
+}
+
+// Each slot is written by one piece and read for the split item that the piece is of; every other
+// item is whole.
+static bool slots_match(const Schedule& s) {
+  std::vector<const CombineItem*> of(size_t(s.slots) + 1, nullptr);  // slot -> its split item
+  for (const CombineItem& c : s.combine)
+    for (int32_t i = 1; i <= c.n; ++i) {
+      if (c.n < 2 || c.slot0 < 0 || c.slot0 + i > s.slots || of[size_t(c.slot0 + i)]) return false;
+      of[size_t(c.slot0 + i)] = &c;
+    }
+  int64_t pieces = 0;
+  for (const WorkItem& w : s.items) {
+    if (w.stream < 0 || w.slot == 0) continue;
+    if (w.slot < 0 || w.slot > s.slots) return false;
+    const CombineItem*& c = of[size_t(w.slot)];
+    if (!c || c->stream != w.stream || c->head != w.head || c->start != w.start || c->len != w.len) return false;
+    c = nullptr;
+    ++pieces;
+  }
+  return pieces == s.slots;
+}
+
 sra_status sra_schedule_info(const sra_problem* p, int which, int64_t* n_items, int64_t* n_spans,
                              int64_t* covered) {
   g_last_error.clear();
@@ -847,9 +890,10 @@ static sra_status expand_call(const sra_problem* p, int which, int32_t sample, i
   if (!out) return fail(SRA_ERR_INVALID_ARGUMENT, "out is NULL");
   Plan P;
   build_plan(L, &P, whole);
-  const Schedule* S = pick(P, which);
-  if (!S) return fail(SRA_ERR_INVALID_ARGUMENT, "unknown schedule");
-  return expand(L, P, *S, which == SRA_SCHED_BWD_DKDV, sample, head, out);
+  Schedule S;
+  if (!launched(P, which, &S)) return fail(SRA_ERR_INVALID_ARGUMENT, "unknown schedule");
+  if (!slots_match(S)) return fail(SRA_ERR_INTERNAL, "pieces and slots of split items do not match");
+  return expand(L, P, S, which == SRA_SCHED_BWD_DKDV, sample, head, out);
 }
 
 sra_status sra_schedule_mask(const sra_problem* p, int which, int32_t sample, uint8_t* out) {
@@ -868,11 +912,24 @@ sra_status sra_launch_info(const sra_problem* p, int which, int64_t* n_items, in
   if (st != SRA_OK) return fail(st, err);
   Plan P;
   build_plan(L, &P);
-  const Schedule* S = pick(P, which);
-  if (!S) return fail(SRA_ERR_INVALID_ARGUMENT, "unknown schedule");
-  if (n_items) *n_items = S->real_items;
-  if (tile) *tile = S->tile;
-  if (split_items) *split_items = int64_t(S->combine.size());
+  Schedule S;
+  if (!launched(P, which, &S)) return fail(SRA_ERR_INVALID_ARGUMENT, "unknown schedule");
+  if (n_items) *n_items = S.real_items;
+  if (tile) *tile = S.tile;
+  if (split_items) *split_items = int64_t(S.combine.size());
+  return SRA_OK;
+}
+
+static sra_status copy_tables(const Schedule& S, int32_t* items, int64_t items_capacity, int32_t* spans,
+                              int64_t spans_capacity) {
+  if (items) {
+    if (items_capacity < int64_t(S.items.size()) * 8) return fail(SRA_ERR_INVALID_ARGUMENT, "items buffer too small");
+    std::memcpy(items, S.items.data(), S.items.size() * sizeof(WorkItem));
+  }
+  if (spans) {
+    if (spans_capacity < int64_t(S.spans.size()) * 4) return fail(SRA_ERR_INVALID_ARGUMENT, "spans buffer too small");
+    std::memcpy(spans, S.spans.data(), S.spans.size() * sizeof(Span));
+  }
   return SRA_OK;
 }
 
@@ -887,15 +944,23 @@ sra_status sra_schedule_export(const sra_problem* p, int which, int32_t* items, 
   build_plan(L, &P, true);
   const Schedule* S = pick(P, which);
   if (!S) return fail(SRA_ERR_INVALID_ARGUMENT, "unknown schedule");
-  if (items) {
-    if (items_capacity < int64_t(S->items.size()) * 8) return fail(SRA_ERR_INVALID_ARGUMENT, "items buffer too small");
-    std::memcpy(items, S->items.data(), S->items.size() * sizeof(WorkItem));
-  }
-  if (spans) {
-    if (spans_capacity < int64_t(S->spans.size()) * 4) return fail(SRA_ERR_INVALID_ARGUMENT, "spans buffer too small");
-    std::memcpy(spans, S->spans.data(), S->spans.size() * sizeof(Span));
-  }
-  return SRA_OK;
+  return copy_tables(*S, items, items_capacity, spans, spans_capacity);
+}
+
+sra_status sra_launch_export(const sra_problem* p, int which, int32_t* items, int64_t items_capacity,
+                             int32_t* spans, int64_t spans_capacity, int64_t* n_items, int64_t* n_spans) {
+  g_last_error.clear();
+  Layout L;
+  std::string err;
+  sra_status st = make_layout(p, &L, &err);
+  if (st != SRA_OK) return fail(st, err);
+  Plan P;
+  build_plan(L, &P);
+  Schedule S;
+  if (!launched(P, which, &S)) return fail(SRA_ERR_INVALID_ARGUMENT, "unknown schedule");
+  if (n_items) *n_items = int64_t(S.items.size());
+  if (n_spans) *n_spans = int64_t(S.spans.size());
+  return copy_tables(S, items, items_capacity, spans, spans_capacity);
 }
 
 sra_status sra_kernel_timing_enable(int enable) {

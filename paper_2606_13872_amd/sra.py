@@ -84,6 +84,7 @@ def lib() -> ctypes.CDLL:
         "sra_launch_mask": [P, ctypes.c_int, i32, i32, vp],
         "sra_dense_mask": [P, i32, vp],
         "sra_schedule_export": [P, ctypes.c_int, vp, i64, vp, i64],
+        "sra_launch_export": [P, ctypes.c_int, vp, i64, vp, i64, ctypes.POINTER(i64), ctypes.POINTER(i64)],
         "sra_release_caches": [],
         "sra_kernel_timing_enable": [ctypes.c_int],
         "sra_kernel_timing": [ctypes.c_int, ctypes.POINTER(ctypes.c_double), ctypes.POINTER(i64)],
@@ -280,6 +281,20 @@ def schedule_export(samples, which: int, heads=1, head_dim=128, flags=0):
     spans = np.zeros((n_spans, 4), dtype=np.int32)
     _check(lib().sra_schedule_export(p.ptr, which, items.ctypes.data_as(ctypes.c_void_p), items.size,
                                      spans.ctypes.data_as(ctypes.c_void_p), spans.size))
+    return items, spans
+
+
+def launch_export(samples, which: int, heads=1, head_dim=128, flags=0):
+    """sra_launch_export: (work items and pieces, spans) of what a call launches."""
+    import numpy as np
+
+    p = Problem(samples, heads, head_dim, flags=flags)
+    n, m = ctypes.c_int64(0), ctypes.c_int64(0)
+    _check(lib().sra_launch_export(p.ptr, which, None, 0, None, 0, ctypes.byref(n), ctypes.byref(m)))
+    items = np.zeros((n.value, 8), dtype=np.int32)
+    spans = np.zeros((m.value, 4), dtype=np.int32)
+    _check(lib().sra_launch_export(p.ptr, which, items.ctypes.data_as(ctypes.c_void_p), items.size,
+                                   spans.ctypes.data_as(ctypes.c_void_p), spans.size, None, None))
     return items, spans
 
 

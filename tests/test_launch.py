@@ -110,3 +110,17 @@ def test_few_gen_rows_and_long_groups_launch_no_empty_pieces(gen, ref, flags):
         got = sra.launch_mask(samples, which, 0, 0, heads=1, flags=flags)
         assert np.array_equal(got, want), which
     assert sra.launch_info(samples, sra.SCHED_BWD_DKDV, heads=1)[2] > 0
+
+
+@pytest.mark.parametrize("name,heads", [("long_keys", 3), ("varlen", 3), ("one_item", 1)])
+def test_the_hooks_show_the_tables_of_a_joint_gradient_launch(name, heads):
+    """dQ and dK/dV items of one launch share its span table; the slots of each kind's pieces are
+    0 .. n - 1, each once."""
+    tables = [sra.launch_export(GEOMS[name], which, heads=heads) for which in SCHEDS[1:]]
+    assert np.array_equal(tables[0][1], tables[1][1])
+    for (items, spans), which in zip(tables, SCHEDS[1:]):
+        n, _, split = sra.launch_info(GEOMS[name], which, heads=heads)
+        assert len(items) == n and set(items[:, 0]) <= {0, 1}
+        assert np.all(items[:, 5] > 0) and np.all(items[:, 4] + items[:, 5] <= len(spans))
+        slots = np.sort(items[items[:, 7] > 0, 7])
+        assert np.array_equal(slots, np.arange(1, len(slots) + 1)) and (len(slots) > 0) == (split > 0)
