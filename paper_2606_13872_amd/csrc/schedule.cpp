@@ -220,11 +220,29 @@ void emit_items(const TileClass& c, int tile, int32_t heads, int step,
     }
 }
 
-// Orders items for launch. Workgroups are dealt round-robin over the 8 XCDs, so item k of
+// Lists items in launch order. Workgroups are dealt round-robin over the 8 XCDs, so item k of
 // the launch order runs on XCD k % 8 and each XCD consumes its own subsequence in order.
 // When heads divide evenly over the XCDs, every head is pinned to one XCD (the rows it streams
-// stay in that XCD's L2) and each XCD's subsequence is longest-first; otherwise the whole list
-// is longest-first and the round-robin deal balances it.
+// stay in that XCD's L2), whose subsequence holds its items in v's order; otherwise the
+// round-robin deal of v balances it.
+void deal_items(const std::vector<WorkItem>& v, int32_t heads, Schedule* s) {
+  s->real_items = int64_t(v.size());
+  s->items.clear();
+  if (heads % kNumXcd != 0) {
+    s->items = v;
+    return;
+  }
+  std::vector<std::vector<WorkItem>> per(kNumXcd);
+  for (const WorkItem& w : v) per[w.head % kNumXcd].push_back(w);
+  size_t n = 0;
+  for (auto& q : per) n = std::max(n, q.size());
+  WorkItem pad{};
+  pad.stream = -1;
+  for (size_t j = 0; j < n; ++j)
+    for (int x = 0; x < kNumXcd; ++x) s->items.push_back(j < per[x].size() ? per[x][j] : pad);
+}
+
+// Orders items for launch, longest first.
 // heads_in_turn: each XCD runs its heads one after another instead, each head's items
 // longest-first. For key tiles, whose items are of a few similar lengths and all stream the
 // head's gen queries from the first row, this keeps the workgroups resident on an XCD on one
@@ -234,23 +252,11 @@ void emit_items(const TileClass& c, int tile, int32_t heads, int step,
 // the next head's start and nearly tripled the misses.
 void order_items(std::vector<std::pair<int64_t, WorkItem>>& v, int32_t heads, bool heads_in_turn, Schedule* s) {
   std::stable_sort(v.begin(), v.end(), [](const auto& a, const auto& b) { return a.first > b.first; });
-  s->real_items = int64_t(v.size());
-  s->items.clear();
-  if (heads % kNumXcd != 0 || v.empty()) {
-    for (auto& e : v) s->items.push_back(e.second);
-    return;
-  }
-  std::vector<std::vector<WorkItem>> per(kNumXcd);
-  for (auto& e : v) per[e.second.head % kNumXcd].push_back(e.second);
-  if (heads_in_turn)
-    for (auto& q : per)
-      std::stable_sort(q.begin(), q.end(), [](const WorkItem& a, const WorkItem& b) { return a.head < b.head; });
-  size_t n = 0;
-  for (auto& q : per) n = std::max(n, q.size());
-  WorkItem pad{};
-  pad.stream = -1;
-  for (size_t j = 0; j < n; ++j)
-    for (int x = 0; x < kNumXcd; ++x) s->items.push_back(j < per[x].size() ? per[x][j] : pad);
+  std::vector<WorkItem> w;
+  for (auto& e : v) w.push_back(e.second);
+  if (heads_in_turn && heads % kNumXcd == 0)
+    std::stable_sort(w.begin(), w.end(), [](const WorkItem& a, const WorkItem& b) { return a.head < b.head; });
+  deal_items(w, heads, s);
 }
 
 // Phase alignment of a schedule (runs after order_items with heads pinned to XCDs). The first
@@ -597,16 +603,19 @@ void split_items(const CostedItems& v, const std::vector<int32_t>& parts, Schedu
   s->spans.swap(spans);
 }
 
-// Leaves of split_items' launch of all rows what the call of the gen queries alone needs: query
-// items and pieces of the gen rows; of key items and pieces (key_major) the gen queries' spans,
-// which come first in every list. Slots are numbered anew, and an item left with one piece is whole:
+// Leaves of the launch of all rows what the call of the gen queries alone needs: query items and
+// pieces of the gen rows; of the key items and pieces of split_items (key_major) the gen queries'
+// spans, which come first in every list. The gen rows' sums then run in one order whether or not the
+// reference queries are computed. Slots are numbered anew, and an item left with one piece is whole:
 // what is dropped would only have added zeros (a reference query whose output has no gradient).
-void keep_gen_queries(bool key_major, Schedule* s) {
+// `heads` as in deal_items, or 1 where items are not dealt to the XCDs.
+void keep_gen_queries(bool key_major, int32_t heads, Schedule* s) {
   std::vector<WorkItem> items;
   std::vector<Span> spans;
   std::map<std::pair<int32_t, int32_t>, int32_t> made;  // (span list's offset, spans kept) -> new offset
   std::vector<int32_t> slot(size_t(s->slots) + 1, 0);   // old slot -> 1 if kept, then the new slot
   for (WorkItem w : s->items) {
+    if (w.stream < 0) continue;
     const Span* l = &s->spans[size_t(w.span_off)];
     if (key_major) {
       int32_t n = 0;
@@ -631,10 +640,9 @@ void keep_gen_queries(bool key_major, Schedule* s) {
     if (c.n > 1) combine.push_back(c);
   }
   for (WorkItem& w : items) w.slot = slot[size_t(w.slot)];
-  s->items.swap(items);
   s->spans.swap(spans);
   s->combine.swap(combine);
-  s->real_items = int64_t(s->items.size());
+  deal_items(items, heads, s);
 }
 
 // Sorts v longest first and returns the items' steps.
@@ -691,21 +699,10 @@ void launch_forward_schedule(const Layout& L, int64_t max_bytes, Schedule* out) 
     parts.swap(k);
     *out = std::move(s);
   }
-  if (L.gen_only) {  // the gen rows' items, as in the call of all rows
-    size_t n = 0;
-    for (size_t i = 0; i < v.size(); ++i)
-      if (v[i].second.stream == 0) {
-        v[n] = v[i];
-        parts[n++] = parts[i];
-      }
-    v.resize(n);
-    parts.resize(n);
-  }
-  if (std::any_of(parts.begin(), parts.end(), [](int32_t k) { return k > 1; })) {
-    split_items(v, parts, out);
-  } else {
-    finish_whole(v, L, kFwdKeyStep, false, out);
-  }
+  const bool split = std::any_of(parts.begin(), parts.end(), [](int32_t k) { return k > 1; });
+  if (split) split_items(v, parts, out);
+  else finish_whole(v, L, kFwdKeyStep, false, out);
+  if (L.gen_only) keep_gen_queries(false, split ? 1 : L.heads, out);
 }
 
 // The backward's launches. Times in units of 0.75 us: a dQ step takes 2.25 us and a dK/dV step 3.0
@@ -728,14 +725,13 @@ void launch_backward_schedules(const Layout& L, Plan* plan) {
   dq.tile = kDqQueryTile;
   dkv.tile = kDkvKeyTile;
   if (vq.size() + vk.size() > size_t(kSplitRounds * kNumCus)) {
+    finish_whole(vq, L, kDqKeyStep, false, &dq);
     if (L.gen_only) {
-      dq = dkv = Schedule();
-      vq = query_major_items(L, kDqQueryTile, kDqKeyStep, &dq);
+      keep_gen_queries(false, L.heads, &dq);
+      dkv = Schedule();
       vk = key_major_items(L, kDkvKeyTile, kDkvQueryStep, &dkv);
-      dq.tile = kDqQueryTile;
       dkv.tile = kDkvKeyTile;
     }
-    finish_whole(vq, L, kDqKeyStep, false, &dq);
     finish_whole(vk, L, kDkvQueryStep, true, &dkv);
     plan->dq = std::move(dq);
     plan->dkv = std::move(dkv);
@@ -761,8 +757,8 @@ void launch_backward_schedules(const Layout& L, Plan* plan) {
   split_items(vk, pk, &dkv);
   split_items(vq, pq, &dq);
   if (L.gen_only) {
-    keep_gen_queries(true, &dkv);
-    keep_gen_queries(false, &dq);
+    keep_gen_queries(true, 1, &dkv);
+    keep_gen_queries(false, 1, &dq);
   }
   Schedule& g = plan->grad;
   std::vector<std::pair<double, WorkItem>> all;

@@ -124,3 +124,44 @@ def test_the_hooks_show_the_tables_of_a_joint_gradient_launch(name, heads):
         assert np.all(items[:, 5] > 0) and np.all(items[:, 4] + items[:, 5] <= len(spans))
         slots = np.sort(items[items[:, 7] > 0, 7])
         assert np.array_equal(slots, np.arange(1, len(slots) + 1)) and (len(slots) > 0) == (split > 0)
+
+
+def _gen_work(samples, which, heads, dim, flags):
+    """(head, start, length) of gen query items and pieces -> their spans, and the split items' pieces
+    in order (slots are numbered per launch)."""
+    items, spans = sra.launch_export(samples, which, heads=heads, head_dim=dim, flags=flags)
+    out = {}
+    for it in items[np.argsort(items[:, 7], kind="stable")]:
+        if it[0] == 0:
+            out.setdefault(tuple(it[1:4]), []).append(spans[it[4]:it[4] + it[5]].tolist())
+    return out
+
+
+def _random_batch(rng):
+    samples = []
+    for _ in range(int(rng.integers(1, 4))):
+        rf = int(rng.integers(0, 13))
+        n = int(rng.integers(4, 60)), int(rng.integers(4, 60))
+        tok = None
+        if rf and rng.random() < 0.2:
+            tok = box_token_mask(rf, *n, int(rng.integers(99)))
+        samples.append(SampleGeom(int(rng.integers(1, 7)), *(n if rng.random() < 0.5 else n[::-1]), rf, *n,
+                                  group_frames=int(rng.integers(1, rf + 2)), ref_token_valid=tok))
+    return samples
+
+
+def test_gen_only_launches_run_the_gen_rows_as_the_call_of_all_rows():
+    """Cached reference K/V: the gen rows' sums run over the same spans in the same order whether or not
+    the reference rows are queries too, so their results are the same bits."""
+    rng = np.random.default_rng(23)
+    calls = [([SampleGeom(6, 33, 54, 9, 33, 54, group_frames=18)], 16, 64),
+             ([SampleGeom(1, 16, 16, 12, 40, 40, group_frames=12), SampleGeom(4, 40, 40, 2, 40, 40)], 16, 128)]
+    calls += [(_random_batch(rng), int(rng.choice([3, 8, 16, 24])), int(rng.choice([64, 128]))) for _ in range(120)]
+    split = 0
+    for samples, heads, dim in calls:
+        for which in SCHEDS[:2]:
+            full = _gen_work(samples, which, heads, dim, 0)
+            gen = _gen_work(samples, which, heads, dim, sra.FLAG_GEN_QUERIES_ONLY)
+            assert gen == full, (samples, heads, dim, which)
+            split += any(len(v) > 1 for v in gen.values())
+    assert 20 < split < 200  # both kinds
