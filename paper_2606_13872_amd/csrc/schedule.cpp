@@ -665,19 +665,26 @@ std::vector<int32_t> sort_steps(CostedItems& v, const Schedule& s) {
   return steps;
 }
 
-// The forward's partial results take no more than kFwdPartialBytes; kTableBytes is more than the
-// tables of any launch that is split (at most kSplitRounds rounds of items and their pieces) take.
+// The forward's partial results take no more than kFwdPartialBytes. kTableBytes is more than the tables
+// of a split launch (at most kSplitRounds rounds of items and their pieces) take, but for calls whose
+// span lists hold thousands of short runs.
 constexpr int64_t kTableBytes = int64_t(4) << 20;
 constexpr int64_t kFwdPartialBytes = int64_t(SRA_NOALLOC_WORKSPACE_MAX) - kTableBytes;
 
 constexpr double kFwdUnitUs = 1.5;  // a 64-key step of 256 rows at d = 128 (1.1 at d = 64)
 
-// The forward's launch: rows per item and splits by the replayed end. A step of the large tile
-// holds 1.5 (d = 128) or 2 (d = 64) times the rows and takes 1.36 or 1.72 times as long (480p, 40
+// A schedule of the call of all rows with whole 256-row items.
+void whole_forward_schedule(const Layout& L, Schedule* out) {
+  CostedItems v = query_major_items(L, kFwdQueryTile, kFwdKeyStep, out);
+  out->tile = kFwdQueryTile;
+  finish_whole(v, L, kFwdKeyStep, false, out);
+}
+
+// The forward's launch of all rows: rows per item and splits by the replayed end. A step of the large
+// tile holds 1.5 (d = 128) or 2 (d = 64) times the rows and takes 1.36 or 1.72 times as long (480p, 40
 // heads: 25.5 -> 23.7 ms; 480p, d = 64, 16 heads: 8.35 -> 7.24 ms). max_bytes: of partial results.
-void launch_forward_schedule(const Layout& L, int64_t max_bytes, Schedule* out) {
-  Layout all = L;
-  all.gen_only = false;
+// Returns whether items are split.
+bool best_forward_schedule(const Layout& L, int64_t max_bytes, Schedule* out) {
   double best = 0;
   CostedItems v;
   std::vector<int32_t> parts;
@@ -685,7 +692,7 @@ void launch_forward_schedule(const Layout& L, int64_t max_bytes, Schedule* out) 
     const bool large = tile != kFwdQueryTile;
     const KernelCost c{!large ? 1.0 : L.head_dim == 128 ? 1.36 : 1.72, 3.0, large ? 3.0 : 2.0, L.head_dim == 128 ? 4.0 : 7.0};
     Schedule s;
-    CostedItems items = query_major_items(all, tile, kFwdKeyStep, &s);
+    CostedItems items = query_major_items(L, tile, kFwdKeyStep, &s);
     const std::vector<int32_t> steps = sort_steps(items, s);
     std::vector<Timed> timed;
     timed.reserve(steps.size());
@@ -702,6 +709,33 @@ void launch_forward_schedule(const Layout& L, int64_t max_bytes, Schedule* out) 
   const bool split = std::any_of(parts.begin(), parts.end(), [](int32_t k) { return k > 1; });
   if (split) split_items(v, parts, out);
   else finish_whole(v, L, kFwdKeyStep, false, out);
+  return split;
+}
+
+// The forward's launch. `fixed`: the rest of its workspace. Where that leaves room in the static scratch
+// of the allocation-free forward, the tables and partial results stay within it wherever those of
+// whole 256-row items do, so that it takes the same calls and runs the same launch.
+void launch_forward_schedule(const Layout& L, int64_t fixed, Schedule* out) {
+  Layout all = L;
+  all.gen_only = false;
+  const int64_t room = int64_t(SRA_NOALLOC_WORKSPACE_MAX) - fixed;  // <= 0: it rejects the call anyway
+  auto need = [&](const Schedule& s) {
+    return int64_t(s.items.size() * sizeof(WorkItem) + s.spans.size() * sizeof(Span) +
+                   s.combine.size() * sizeof(CombineItem)) + s.slots * slot_bytes(s.tile, L.head_dim, 1, 2);
+  };
+  int64_t bytes = room <= 0 ? kFwdPartialBytes : std::max<int64_t>(0, std::min(kFwdPartialBytes, room - kTableBytes));
+  bool split = best_forward_schedule(all, bytes, out);
+  for (bool last : {false, true}) {  // larger tables than reckoned: as much less for the partial results, or none
+    if (room <= 0 || need(*out) <= room || !split) break;
+    bytes = last ? 0 : std::max<int64_t>(0, bytes - (need(*out) - room));
+    *out = Schedule();
+    split = best_forward_schedule(all, bytes, out);
+  }
+  if (room > 0 && need(*out) > room) {  // phases of the larger tile may copy long span lists more often
+    Schedule s;
+    whole_forward_schedule(all, &s);
+    if (need(s) <= room) *out = std::move(s);
+  }
   if (L.gen_only) keep_gen_queries(false, split ? 1 : L.heads, out);
 }
 
@@ -838,19 +872,22 @@ void build_plan(const Layout& L_in, Plan* plan, bool whole) {
   else
     plan->exec = L_in;
   const Layout& L = plan->exec;
+  plan->fill.clear();
+  for (const SampleLayout& sm : L.samples) {  // the gaps between valid ref runs
+    int64_t r = 0;
+    for (const auto& v : sm.vruns) {
+      if (v.first > r) plan->fill.push_back({1, int32_t(sm.ref_off + r), int32_t(v.first - r), 0});
+      r = v.second;
+    }
+    if (r < sm.R) plan->fill.push_back({1, int32_t(sm.ref_off + r), int32_t(sm.R - r), 0});
+  }
   plan->fwd = plan->dq = plan->dkv = Schedule();
   if (whole) {
-    CostedItems v = query_major_items(L, kFwdQueryTile, kFwdKeyStep, &plan->fwd);
-    finish_whole(v, L, kFwdKeyStep, false, &plan->fwd);
-    plan->fwd.tile = kFwdQueryTile;
+    whole_forward_schedule(L, &plan->fwd);
   } else {
-    // The partial results and the rest of the forward's workspace stay within the static scratch
-    // of the allocation-free forward wherever the rest does, so that it takes the same calls and
-    // runs the same launch.
-    const int64_t ref = plan->compacted ? L.sum_ref * (L.heads * (8 * int64_t(L.head_dim) + 4) + 4) + L_in.sum_ref * 4 : 0;
-    const int64_t room = int64_t(SRA_NOALLOC_WORKSPACE_MAX) - ref;  // <= 0: it rejects the call anyway
-    launch_forward_schedule(L, room <= 0 ? kFwdPartialBytes : std::max<int64_t>(0, std::min(kFwdPartialBytes, room - kTableBytes)),
-                            &plan->fwd);
+    int64_t fixed = int64_t(plan->fill.size() * sizeof(FillRange)) + 16 * 256;  // and every part's alignment
+    if (plan->compacted) fixed += L.sum_ref * (L.heads * (8 * int64_t(L.head_dim) + 4) + 4) + L_in.sum_ref * 4;
+    launch_forward_schedule(L, fixed, &plan->fwd);
   }
   plan->grad_joint = false;
   plan->grad = Schedule();
@@ -861,15 +898,6 @@ void build_plan(const Layout& L_in, Plan* plan, bool whole) {
     finish_whole(vk, L, kDkvQueryStep, true, &plan->dkv);
   } else {
     launch_backward_schedules(L, plan);
-  }
-  plan->fill.clear();
-  for (const SampleLayout& sm : L.samples) {  // the gaps between valid ref runs
-    int64_t r = 0;
-    for (const auto& v : sm.vruns) {
-      if (v.first > r) plan->fill.push_back({1, int32_t(sm.ref_off + r), int32_t(v.first - r), 0});
-      r = v.second;
-    }
-    if (r < sm.R) plan->fill.push_back({1, int32_t(sm.ref_off + r), int32_t(sm.R - r), 0});
   }
 }
 

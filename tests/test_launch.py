@@ -165,3 +165,13 @@ def test_gen_only_launches_run_the_gen_rows_as_the_call_of_all_rows():
             assert gen == full, (samples, heads, dim, which)
             split += any(len(v) > 1 for v in gen.values())
     assert 20 < split < 200  # both kinds
+
+
+@pytest.mark.parametrize("flags", [sra.FLAG_GEN_WINDOW, sra.FLAG_GEN_WINDOW | sra.FLAG_GEN_QUERIES_ONLY])
+@pytest.mark.parametrize("gen_frames,ref_frames", [(300, 2400), (280, 3000), (300, 3400), (330, 2800), (100, 3800)])
+def test_long_span_lists_leave_the_allocation_free_forward_its_calls(gen_frames, ref_frames, flags):
+    """Window tiles that each list a thousand and more one-token runs: 3 to 8 MB of tables, beside which the
+    partial results have to fit."""
+    valid = tuple(int(i % 2 == 0) for i in range(ref_frames))
+    samples = [SampleGeom(gen_frames, 1, 2, ref_frames, 1, 1, frame_valid=valid, gen_window=0)]
+    assert sra.Problem(samples, 1, 128, flags=flags).workspace_size(False) <= sra.noalloc_workspace_max()
