@@ -77,3 +77,19 @@ def test_keys_masked_by_an_infinite_head_dim(heads, d, masked):
         assert float((lse[h].double().cpu() - torch.logsumexp(sc, -1)).abs().max()) < 1e-3
         want = torch.softmax(sc, -1) @ v[:, h]
         assert float((o[:, h].double().cpu() - want).norm() / want.norm()) < 1e-2  # bf16 P and O: 2.5e-3
+
+
+@pytest.mark.parametrize("heads,d,split", [(3, 128, True), (1, 64, True), (40, 128, False), (24, 64, False), (80, 128, False),
+                                           (80, 64, False)])
+def test_rows_masked_by_an_infinite_head_dim(heads, d, split):
+    """Rows whose scores are all -inf have LSE = -inf (and O = 0 / 0), in a whole item as in a split one."""
+    s = SampleGeom(2, 20, 20, 3, 13, 11)
+    assert (sra.launch_info([s], sra.SCHED_FORWARD, heads=heads, head_dim=d)[2] > 0) == split
+    print(f"[masked rows] heads {heads} d {d} split {split}", flush=True)
+    x = make_inputs([s], heads, d, 71, device="cuda")
+    x["q_gen"][:, :, 0] = 1
+    for n in ("k_gen", "k_ref"):
+        x[n][:, :, 0] = float("-inf")
+    o, _, lse, _ = sra.forward(*[x[n] for n in ("q_gen", "k_gen", "v_gen", "q_ref", "k_ref", "v_ref")], [s])
+    torch.cuda.synchronize()
+    assert bool((lse == float("-inf")).all()) and bool(o.isnan().all())
