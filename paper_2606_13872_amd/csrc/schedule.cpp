@@ -265,9 +265,10 @@ void order_items(std::vector<std::pair<int64_t, WorkItem>>& v, int32_t heads, bo
 // on an XCD share them through its L2 only while they are at nearby steps of the span at the
 // same time. Tiles start whenever a compute unit frees up, so tiles of different lengths drift
 // apart. Here each XCD's launch order is replayed on its compute units (one resident tile
-// each, time counted in steps of the inner loop): a tile predicted to start at time t begins
-// its first span at step t mod S (S = the span's steps) and wraps around, so that all tiles
-// stream step t mod S at time t. The tile's pairs are unchanged (the span is cut in two); only
+// each, time counted in steps of `step` rows: in what is launched the LDS tile of the kernels, so
+// that a span is cut where a tile ends): a tile predicted to start at time t begins its first span
+// at step t mod S (S = the span's steps) and wraps around, so that all tiles stream step t mod S
+// at time t. The tile's pairs are unchanged (the span is cut in two); only
 // the order of the sums changes, fixed by the plan.
 void align_phases(int step, Schedule* s) {
   std::vector<Span> spans;
@@ -754,19 +755,19 @@ void launch_backward_schedules(const Layout& L, Plan* plan) {
   Layout full = L;
   full.gen_only = false;
   Schedule dq, dkv;
-  CostedItems vq = query_major_items(full, kDqQueryTile, kDqKeyStep, &dq);
-  CostedItems vk = key_major_items(full, kDkvKeyTile, kDkvQueryStep, &dkv);
+  CostedItems vq = query_major_items(full, kDqQueryTile, kStep, &dq);
+  CostedItems vk = key_major_items(full, kDkvKeyTile, kStep, &dkv);
   dq.tile = kDqQueryTile;
   dkv.tile = kDkvKeyTile;
   if (vq.size() + vk.size() > size_t(kSplitRounds * kNumCus)) {
-    finish_whole(vq, L, kDqKeyStep, false, &dq);
+    finish_whole(vq, L, kStep, false, &dq);
     if (L.gen_only) {
       keep_gen_queries(false, L.heads, &dq);
       dkv = Schedule();
-      vk = key_major_items(L, kDkvKeyTile, kDkvQueryStep, &dkv);
+      vk = key_major_items(L, kDkvKeyTile, kStep, &dkv);
       dkv.tile = kDkvKeyTile;
     }
-    finish_whole(vk, L, kDkvQueryStep, true, &dkv);
+    finish_whole(vk, L, kStep, true, &dkv);
     plan->dq = std::move(dq);
     plan->dkv = std::move(dkv);
     return;

@@ -13,7 +13,8 @@ constexpr int kFwdKeyStep = 64;
 constexpr int fwd_large_tile(int head_dim) { return head_dim == 128 ? 384 : 512; }
 // dQ kernel of the backward: 256-row query tiles, held by 4 wave64s (one per
 // SIMD, 64 query rows each); keys stream through LDS 64 at a time. kDqKeyStep and kDkvQueryStep
-// are the steps in which the scheduler counts a long launch's phases.
+// are the steps in which the whole schedules of the inspection hooks count phases; what is launched
+// counts them in kStep.
 constexpr int kDqQueryTile = 256;
 constexpr int kDqKeyStep = 32;
 // dK/dV kernel of the backward: 4 wave64s (one per SIMD) x 64 keys = 256 keys per work item;

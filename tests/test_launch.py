@@ -175,3 +175,14 @@ def test_long_span_lists_leave_the_allocation_free_forward_its_calls(gen_frames,
     valid = tuple(int(i % 2 == 0) for i in range(ref_frames))
     samples = [SampleGeom(gen_frames, 1, 2, ref_frames, 1, 1, frame_valid=valid, gen_window=0)]
     assert sra.Problem(samples, 1, 128, flags=flags).workspace_size(False) <= sra.noalloc_workspace_max()
+
+
+@pytest.mark.parametrize("which", SCHEDS)
+def test_launched_phases_cut_spans_at_tile_ends(which):
+    """Long launches with heads pinned to XCDs start a gen span part way in: at a whole number of the
+    kernels' 64-row tiles, since a part that ends elsewhere costs a ragged tile of its own."""
+    samples = [SampleGeom(11, 35, 41, 5, 35, 41)]
+    items, spans = sra.launch_export(samples, which, heads=24)
+    first = spans[np.unique(items[items[:, 0] >= 0, 4])]
+    assert np.all(first[first[:, 0] == 0, 1] % 64 == 0)
+    assert (first[first[:, 0] == 0, 1] > 0).sum() >= 3
