@@ -499,8 +499,8 @@ double partials_us(int64_t bytes) {
 // parts, and the same for only those items of the long ones that a last, partial round of the
 // compute units would hold. Not for launches of over kSplitRounds rounds: there the order that keeps
 // items of a head in step on an XCD is worth more than the last round. unit_us: one unit of the
-// times in microseconds.
-std::vector<int32_t> choose_split(const std::vector<Timed>& v, int64_t max_bytes, double unit_us, double* end) {
+// times in microseconds. A launch that ends before `least` stays whole.
+std::vector<int32_t> choose_split(const std::vector<Timed>& v, int64_t max_bytes, double unit_us, double least, double* end) {
   const size_t n = v.size();
   std::vector<int32_t> best(n, 1);
   *end = 0;
@@ -536,6 +536,7 @@ std::vector<int32_t> choose_split(const std::vector<Timed>& v, int64_t max_bytes
   };
   *end = eval(chosen, 0);
   const double whole = *end;
+  if (whole < least) return best;
   for (int32_t parts = 2; parts <= 24; ++parts) {
     for (int tail = 0; tail < (rounds > 0 ? 2 : 1); ++tail) {
       int64_t bytes = 0;
@@ -674,6 +675,12 @@ constexpr int64_t kFwdPartialBytes = int64_t(SRA_NOALLOC_WORKSPACE_MAX) - kTable
 
 constexpr double kFwdUnitUs = 1.5;  // a 64-key step of 256 rows at d = 128 (1.1 at d = 64)
 
+// 64-wide heads' launches that end before this (items of up to 16 steps) take about as long as the
+// host's part of a call, which a split makes a launch longer: calls in a row go from 27.4-29.0 to
+// 29.6-32.0 us (a call waited for from 52-55 to 47-52 us). Of 17 to 19 steps they go from 27.5-32.7 to
+// 19.5-27.5 us. At d = 128 the shortest calls split, of 9 and 10 steps, go from 21.6-31.2 to 19.9-31.3.
+constexpr double kFwdLeast64 = 19.5;
+
 // A schedule of the call of all rows with whole 256-row items.
 void whole_forward_schedule(const Layout& L, Schedule* out) {
   CostedItems v = query_major_items(L, kFwdQueryTile, kFwdKeyStep, out);
@@ -686,6 +693,7 @@ void whole_forward_schedule(const Layout& L, Schedule* out) {
 // heads: 25.5 -> 23.7 ms; 480p, d = 64, 16 heads: 8.35 -> 7.24 ms). max_bytes: of partial results.
 // Returns whether items are split.
 bool best_forward_schedule(const Layout& L, int64_t max_bytes, Schedule* out) {
+  const double least = L.head_dim == 64 ? kFwdLeast64 : 0.0;
   double best = 0;
   CostedItems v;
   std::vector<int32_t> parts;
@@ -699,13 +707,14 @@ bool best_forward_schedule(const Layout& L, int64_t max_bytes, Schedule* out) {
     timed.reserve(steps.size());
     for (int32_t n : steps) timed.push_back({n, &c, slot_bytes(tile, L.head_dim, 1, 2)});
     double end;
-    std::vector<int32_t> k = choose_split(timed, max_bytes, kFwdUnitUs, &end);
+    std::vector<int32_t> k = choose_split(timed, max_bytes, kFwdUnitUs, least, &end);
     if (large && !(end < 0.99 * best)) continue;
     best = end;
     s.tile = tile;
     v.swap(items);
     parts.swap(k);
     *out = std::move(s);
+    if (best < least && std::all_of(parts.begin(), parts.end(), [](int32_t k) { return k == 1; })) break;
   }
   const bool split = std::any_of(parts.begin(), parts.end(), [](int32_t k) { return k > 1; });
   if (split) split_items(v, parts, out);
@@ -783,7 +792,7 @@ void launch_backward_schedules(const Layout& L, Plan* plan) {
   std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return timed[a].time() > timed[b].time(); });
   for (int32_t i : order) sorted.push_back(timed[i]);
   double end;
-  const std::vector<int32_t> k = choose_split(sorted, kBwdPartialBytes, kBwdUnitUs, &end);
+  const std::vector<int32_t> k = choose_split(sorted, kBwdPartialBytes, kBwdUnitUs, 0.0, &end);
   std::vector<int32_t> pk(vk.size()), pq(vq.size());
   for (size_t i = 0; i < order.size(); ++i) {
     if (size_t(order[i]) < vk.size()) pk[order[i]] = k[i];

@@ -186,3 +186,12 @@ def test_launched_phases_cut_spans_at_tile_ends(which):
     first = spans[np.unique(items[items[:, 0] >= 0, 4])]
     assert np.all(first[first[:, 0] == 0, 1] % 64 == 0)
     assert (first[first[:, 0] == 0, 1] > 0).sum() >= 3
+
+
+@pytest.mark.parametrize("dim,whole,split", [(64, 16, 17), (128, 8, 9)])
+def test_short_forwards_stay_whole(dim, whole, split):
+    """A launch that ends within the host's part of a call is not split."""
+    def info(steps):
+        return sra.launch_info([SampleGeom(1, 2, 32, 1, 64, steps - 1)], sra.SCHED_FORWARD, heads=2, head_dim=dim)
+    assert info(whole)[2] == 0
+    assert info(split)[2] > 0
