@@ -18,7 +18,7 @@ CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libsra.so")
 
-SOURCES = ["schedule.cpp", "sra_api.cpp", "sra_fwd.hip", "sra_bwd.hip", "sra_grad.hip",
+SOURCES = ["schedule.cpp", "sra_api.cpp", "sra_fwd.hip", "sra_fwd32.hip", "sra_bwd.hip", "sra_grad.hip",
            "sra_compact.hip", "sra_noalloc.hip"]
 
 COMMON = [

@@ -685,21 +685,27 @@ constexpr double kFwdLeast64 = 19.5;
 void whole_forward_schedule(const Layout& L, Schedule* out) {
   CostedItems v = query_major_items(L, kFwdQueryTile, kFwdKeyStep, out);
   out->tile = kFwdQueryTile;
+  out->mfma32 = true;
   finish_whole(v, L, kFwdKeyStep, false, out);
 }
 
 // The forward's launch of all rows: rows per item and splits by the replayed end. A step of the large
-// tile holds 1.5 (d = 128) or 2 (d = 64) times the rows and takes 1.36 or 1.72 times as long (480p, 40
-// heads: 25.5 -> 23.7 ms; 480p, d = 64, 16 heads: 8.35 -> 7.24 ms). max_bytes: of partial results.
+// tile holds 1.5 (d = 128) or 2 (d = 64) times the rows and takes 1.36 or 1.78 times as long (480p, 40
+// heads: 25.5 -> 23.7 ms; 480p, d = 64, 16 heads: 8.11 -> 7.18 ms). max_bytes: of partial results.
 // Returns whether items are split.
+// 256-row items run on 32x32x16 MFMAs (mfma32) but for d = 128 where the launch fills the chip for long
+// enough that the board's power limit sets in: more items than compute units, of 20 steps or more,
+// 110 us of steps each. There 16x16x32 MFMAs are the faster (840 items, 286 us: 4 %; 743, 2.18 ms: 3.5 %;
+// 352, 181 us: 2.5 %), elsewhere 32x32x16 ones (148 items, 394 us: 10 %; 456, 109 us: 8 %; 1,840 of 13
+// steps, 192 us: 6 %). At d = 64 they are at every size (2.44 ms: 5 %).
 bool best_forward_schedule(const Layout& L, int64_t max_bytes, Schedule* out) {
   const double least = L.head_dim == 64 ? kFwdLeast64 : 0.0;
-  double best = 0;
+  double best = 0, total = 0;
   CostedItems v;
   std::vector<int32_t> parts;
   for (int tile : {kFwdQueryTile, fwd_large_tile(L.head_dim)}) {
     const bool large = tile != kFwdQueryTile;
-    const KernelCost c{!large ? 1.0 : L.head_dim == 128 ? 1.36 : 1.72, 3.0, large ? 3.0 : 2.0, L.head_dim == 128 ? 4.0 : 7.0};
+    const KernelCost c{!large ? 1.0 : L.head_dim == 128 ? 1.36 : 1.78, 3.0, large ? 3.0 : 2.0, L.head_dim == 128 ? 4.0 : 7.0};
     Schedule s;
     CostedItems items = query_major_items(L, tile, kFwdKeyStep, &s);
     const std::vector<int32_t> steps = sort_steps(items, s);
@@ -710,6 +716,7 @@ bool best_forward_schedule(const Layout& L, int64_t max_bytes, Schedule* out) {
     std::vector<int32_t> k = choose_split(timed, max_bytes, kFwdUnitUs, least, &end);
     if (large && !(end < 0.99 * best)) continue;
     best = end;
+    total = std::accumulate(steps.begin(), steps.end(), 0.0);
     s.tile = tile;
     v.swap(items);
     parts.swap(k);
@@ -717,6 +724,9 @@ bool best_forward_schedule(const Layout& L, int64_t max_bytes, Schedule* out) {
     if (best < least && std::all_of(parts.begin(), parts.end(), [](int32_t k) { return k == 1; })) break;
   }
   const bool split = std::any_of(parts.begin(), parts.end(), [](int32_t k) { return k > 1; });
+  const double n = std::accumulate(parts.begin(), parts.end(), 0.0);
+  out->mfma32 = out->tile == kFwdQueryTile &&
+                (L.head_dim == 64 || n <= kNumCus || total < 20 * n || total * kFwdUnitUs < 110.0 * kNumCus);
   if (split) split_items(v, parts, out);
   else finish_whole(v, L, kFwdKeyStep, false, out);
   return split;

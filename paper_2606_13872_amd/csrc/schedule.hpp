@@ -45,6 +45,7 @@ struct Schedule {
   std::vector<CombineItem> combine;  // split items
   int32_t slots = 0;                 // their pieces
   int32_t tile = 0;                  // rows per work item
+  bool mfma32 = false;               // forward: 256-row items on 32x32x16 MFMAs
 };
 
 // When a token mask splits reference frames into many short runs of valid tokens, tiles cut

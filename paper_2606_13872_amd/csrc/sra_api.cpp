@@ -518,7 +518,7 @@ sra_status forward_call(const sra_problem* p, const void* q_gen, const void* k_g
     a.lse[1] = lse_c;
   }
   e = timed(SRA_KERNEL_FORWARD, s, [&] {
-    const hipError_t x = launch_forward(a, int(P.fwd.items.size()), L.head_dim, s);
+    const hipError_t x = launch_forward(a, int(P.fwd.items.size()), L.head_dim, P.fwd.mfma32, s);
     if (x != hipSuccess) return x;
     return launch_forward_combine(a, reinterpret_cast<const CombineItem*>(ws + cp->fwd.offsets[5]),
                                   int(P.fwd.combine.size()), L.head_dim, s);

@@ -1,13 +1,19 @@
 // Device helpers for the gfx950 (CDNA4) SRA kernels: MFMA, LDS transpose reads, wave64
 // reductions over the lanes of an output column.
 //
-// Lane layouts of V_MFMA_F32_16X16X32_BF16 used throughout (lane l of a wave64):
+// Lane layouts of V_MFMA_F32_16X16X32_BF16 (lane l of a wave64):
 //   A (16 x 32): lane l holds A[l%16][8*(l/16) + j], j = 0..7
 //   B (32 x 16): lane l holds B[8*(l/16) + j][l%16]
 //   C (16 x 16): register i of lane l holds C[4*(l/16) + i][l%16]
 // So lanes l, l+16, l+32 and l+48 share one output column and split its 16 rows between them,
 // and two C blocks of 16 rows, packed to bf16, are a B fragment of the product over those 32 rows
 // (k slots 8 g + 0..3 = rows 4 g + i of the first, 8 g + 4..7 of the second).
+//
+// V_MFMA_F32_32X32X16_BF16, of the forward's 256-row items on short calls:
+//   A (32 x 16): lane l holds A[l%32][8*(l/32) + j], j = 0..7
+//   B (16 x 32): lane l holds B[8*(l/32) + j][l%32]
+//   C (32 x 32): register i of lane l holds C[8*(i/4) + 4*(l/32) + i%4][l%32]
+// So lanes l and l+32 share one output column and split its 32 rows between them.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -21,6 +27,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 typedef bf16x4 __attribute__((address_space(3))) lds_bf16x4;
 
@@ -37,6 +44,10 @@ __device__ __forceinline__ void static_for(F f) {
 
 __device__ __forceinline__ floatx4 mfma16(bf16x8 a, bf16x8 b, floatx4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
+__device__ __forceinline__ floatx16 mfma32(bf16x8 a, bf16x8 b, floatx16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
 // acc += A B with the accumulator pinned to AGPRs. For kernels whose accumulators fill the
@@ -63,7 +74,7 @@ __device__ __forceinline__ bf16x8 ld8(const __bf16* p) { return *reinterpret_cas
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// Combine a value held by lanes l and l^32 (the two halves of one MFMA output column).
+// Combine a value held by lanes l and l^32 (the two halves of one 32x32 MFMA output column).
 __device__ __forceinline__ float pair_max(float x) {
   auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   return __builtin_elementwise_maximum(__uint_as_float(s[0]), __uint_as_float(s[1]));

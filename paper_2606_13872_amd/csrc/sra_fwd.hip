@@ -13,10 +13,11 @@
 //   O^T (d x queries) += V^T P^T          V^T fragments via the LDS transpose read
 //
 // 16x16x32 MFMAs: at the board's power limit they sustain 2,050 TFLOP/s from registers on
-// random data, 32x32x16 ones 1,840 (one wave per SIMD) or 1,350 (two).
+// random data, 32x32x16 ones 1,840 (one wave per SIMD) or 1,350 (two). Launches that end before that
+// limit sets in run on 32x32x16 ones (sra_fwd32.hip).
 //
-// Bound by MFMA issue at the board's power limit, then by what one 16-row block costs in LDS reads: 32 rows
-// per wave feed two MFMAs per fragment, 48 (d = 128) three, 64 (d = 64) four. 480p layer, 40 heads:
+// What one 16-row block costs in LDS reads falls with the rows per wave: 32 rows (d = 128, 256-row
+// items) feed two MFMAs per fragment, 48 (d = 128) three, 64 (d = 64) four. 480p layer, 40 heads:
 // 26.2 ms with 32x32x16 MFMAs, 25.5 with these, 23.8 (1,340 TFLOP/s) with 48 rows.
 //
 // The key loop is software-pipelined in 32-key halves and each wave's instruction stream is
@@ -531,16 +532,12 @@ static void launch_tile(const FwdArgs& a, int n_items, hipStream_t stream) {
     hipLaunchKernelGGL((sra_fwd_kernel<D, NQ, 2>), grid, block, 0, stream, a);
 }
 
-hipError_t launch_forward(const FwdArgs& a, int n_items, int head_dim, hipStream_t stream) {
+hipError_t launch_forward(const FwdArgs& a, int n_items, int head_dim, bool mfma32, hipStream_t stream) {
   if (n_items <= 0) return hipSuccess;
-  const bool large = a.tile != kFwdQueryTile;
-  if (head_dim == 128) {
-    if (large) launch_tile<128, fwd_large_tile(128) / 128>(a, n_items, stream);
-    else launch_tile<128, kFwdQueryTile / 128>(a, n_items, stream);
-  } else {
-    if (large) launch_tile<64, fwd_large_tile(64) / 128>(a, n_items, stream);
-    else launch_tile<64, kFwdQueryTile / 128>(a, n_items, stream);
-  }
+  if (mfma32) return launch_forward32(a, n_items, head_dim, stream);
+  if (head_dim == 64) launch_tile<64, fwd_large_tile(64) / 128>(a, n_items, stream);
+  else if (a.tile == kFwdQueryTile) launch_tile<128, kFwdQueryTile / 128>(a, n_items, stream);
+  else launch_tile<128, fwd_large_tile(128) / 128>(a, n_items, stream);
   return hipGetLastError();
 }
 

@@ -6,7 +6,7 @@
 
 namespace sra {
 
-hipError_t launch_forward(const FwdArgs&, int, int, hipStream_t) { return hipErrorNotSupported; }
+hipError_t launch_forward(const FwdArgs&, int, int, bool, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_forward_combine(const FwdArgs&, const CombineItem*, int, int, hipStream_t) {
   return hipErrorNotSupported;
 }

@@ -96,7 +96,9 @@ struct ScatterArgs {
   int32_t heads;
 };
 
-hipError_t launch_forward(const FwdArgs& a, int n_items, int head_dim, hipStream_t stream);
+// Items of a.tile rows; mfma32: 256-row ones on 32x32x16 MFMAs (sra_fwd32.hip).
+hipError_t launch_forward(const FwdArgs& a, int n_items, int head_dim, bool mfma32, hipStream_t stream);
+hipError_t launch_forward32(const FwdArgs& a, int n_items, int head_dim, hipStream_t stream);
 hipError_t launch_forward_combine(const FwdArgs& a, const CombineItem* items, int n, int head_dim, hipStream_t stream);
 hipError_t launch_delta(const DeltaArgs& a, int head_dim, hipStream_t stream);
 hipError_t launch_grad(GradKind kind, const BwdArgs& a, int n_items, int head_dim, hipStream_t stream);

@@ -12,6 +12,12 @@ namespace sra {
 // together): a stride of D + 16 serves both without bank conflicts (measured 4.5 and 2.6 cycles
 // per wave read; D + 8 takes 8.2 and 4.3, D + 24 8.2 and 4.3).
 template <int D> constexpr int kPadRS = D + 16;
+// 32x32x16 MFMAs take 32 rows per fragment: row fragments of 32 rows x 32 bytes and transpose reads of
+// 4 rows x 4 chunks, both at 128 bytes per clock with a stride of D + 8 and, for the transpose
+// reads, the rows of each block of 16 permuted: logical row r = 4a + b (a, b < 4) sits at physical
+// row 4b + a. The map is its own inverse, and for r < 8 it sends r + 8 to perm16(r) + 2.
+template <int D> constexpr int kPadRS32 = D + 8;
+__host__ __device__ constexpr int perm16(int r) { return (r & ~15) | ((r & 3) << 2) | ((r >> 2) & 3); }
 
 template <int D, int NR, int RS>
 struct PaddedTile {
@@ -175,8 +181,9 @@ __device__ __forceinline__ void lds_dma_x1_off(uint64_t base, uint32_t off, uint
 // into a padded tile. Each wave instruction fills 1 KB of LDS: lane l writes the 16 bytes at
 // (LDS base + 16 l), so lane l fetches the global chunk that belongs there; lanes that land on
 // a pad slot fetch an in-bounds chunk that nothing reads. Rows past the span end are clamped
-// to its last row (the kernels mask them). Instructions are dealt over the NW waves.
-template <int D, int NR, int RS, int NW>
+// to its last row (the kernels mask them). Instructions are dealt over the NW waves. kPerm: rows
+// permuted in blocks of 16 (perm16).
+template <int D, int NR, int RS, int NW, bool kPerm = false>
 __device__ __forceinline__ void tile_load_lds(__bf16* lds, const __bf16* __restrict__ src, int64_t stride,
                                               int head, int start, int len, int off, int wave) {
   using TL = PaddedTile<D, NR, RS>;
@@ -187,7 +194,8 @@ __device__ __forceinline__ void tile_load_lds(__bf16* lds, const __bf16* __restr
     const int ins = wave + j * NW;
     if (ins < TL::kInstr) {
       const int p = ins * 64 + lane;
-      const int row = min(p / SPR, NR - 1);
+      const int prow = min(p / SPR, NR - 1);
+      const int row = kPerm ? perm16(prow) : prow;
       const int slot = p % SPR;
       const int ch = slot < CPR ? slot : 0;
       const int rr = min(off + row, len - 1);
@@ -199,7 +207,7 @@ __device__ __forceinline__ void tile_load_lds(__bf16* lds, const __bf16* __restr
 
 // Per-lane address offsets of the direct loads of a padded tile, for tiles whose NR rows all
 // lie inside the span (no clamping): lane offsets are fixed, only the tile's first row moves.
-template <int D, int NR, int RS, int NW>
+template <int D, int NR, int RS, int NW, bool kPerm = false>
 struct TileLoader {
   using TL = PaddedTile<D, NR, RS>;
   static constexpr int kSlots = (TL::kInstr + NW - 1) / NW;
@@ -210,7 +218,8 @@ struct TileLoader {
 #pragma unroll
     for (int j = 0; j < kSlots; ++j) {
       const int p = (wave + j * NW) * 64 + lane;
-      const int row = min(p / SPR, NR - 1);
+      const int prow = min(p / SPR, NR - 1);
+      const int row = kPerm ? perm16(prow) : prow;
       const int slot = p % SPR;
       voff[j] = int(row * stride) + head * D + (slot < CPR ? slot : 0) * 8;
     }
