@@ -675,11 +675,14 @@ constexpr int64_t kFwdPartialBytes = int64_t(SRA_NOALLOC_WORKSPACE_MAX) - kTable
 
 constexpr double kFwdUnitUs = 1.5;  // a 64-key step of 256 rows at d = 128 (1.1 at d = 64)
 
-// 64-wide heads' launches that end before this (items of up to 16 steps) take about as long as the
-// host's part of a call, which a split makes a launch longer: calls in a row go from 27.4-29.0 to
-// 29.6-32.0 us (a call waited for from 52-55 to 47-52 us). Of 17 to 19 steps they go from 27.5-32.7 to
-// 19.5-27.5 us. At d = 128 the shortest calls split, of 9 and 10 steps, go from 21.6-31.2 to 19.9-31.3.
-constexpr double kFwdLeast64 = 19.5;
+// Launches that end before this take about as long as the host's part of a call, which a split makes a
+// launch longer. d = 64, items of up to 16 steps: calls in a row 27.4-29.0 us whole, 29.6-32.0 split
+// (a call waited for 52-55 and 47-52); of 17 to 19 steps 27.5-32.7 and 19.5-27.5. d = 128, 9 and 10
+// steps: 21.6-31.2 whole, 19.9-31.3 split. Steps of items of up to 128 rows, one wave per SIMD, take
+// 0.7 of the time (128 and 192 rows: 0.76 and 1.09 us at d = 128, 0.66 and 0.97 at d = 64): of 9 and
+// 10 steps at d = 128 23.7 and 28.7 whole, 26.2 and 30.8 split.
+constexpr double kFwdLeast[2] = {19.5, 11.5};  // d = 64, 128
+constexpr double kFwdHalfStep = 0.7;
 
 // A schedule of the call of all rows with whole 256-row items.
 void whole_forward_schedule(const Layout& L, Schedule* out) {
@@ -699,7 +702,7 @@ void whole_forward_schedule(const Layout& L, Schedule* out) {
 // 352, 181 us: 2.5 %), elsewhere 32x32x16 ones (148 items, 394 us: 10 %; 456, 109 us: 8 %; 1,840 of 13
 // steps, 192 us: 6 %). At d = 64 they are at every size (2.44 ms: 5 %).
 bool best_forward_schedule(const Layout& L, int64_t max_bytes, Schedule* out) {
-  const double least = L.head_dim == 64 ? kFwdLeast64 : 0.0;
+  double least = kFwdLeast[L.head_dim == 128];
   double best = 0, total = 0;
   CostedItems v;
   std::vector<int32_t> parts;
@@ -712,6 +715,11 @@ bool best_forward_schedule(const Layout& L, int64_t max_bytes, Schedule* out) {
     std::vector<Timed> timed;
     timed.reserve(steps.size());
     for (int32_t n : steps) timed.push_back({n, &c, slot_bytes(tile, L.head_dim, 1, 2)});
+    if (!large) {  // the rows of the items that decide when the launch ends
+      int32_t rows = 0;
+      for (size_t i = 0; i < items.size() && 2 * steps[i] >= steps[0]; ++i) rows = std::max(rows, items[i].second.len);
+      if (rows <= kFwdQueryTile / 2) least /= kFwdHalfStep;
+    }
     double end;
     std::vector<int32_t> k = choose_split(timed, max_bytes, kFwdUnitUs, least, &end);
     if (large && !(end < 0.99 * best)) continue;

@@ -188,10 +188,12 @@ def test_launched_phases_cut_spans_at_tile_ends(which):
     assert (first[first[:, 0] == 0, 1] > 0).sum() >= 3
 
 
-@pytest.mark.parametrize("dim,whole,split", [(64, 16, 17), (128, 8, 9)])
-def test_short_forwards_stay_whole(dim, whole, split):
-    """A launch that ends within the host's part of a call is not split."""
+@pytest.mark.parametrize("dim,rows,whole,split", [(64, 64, 24, 25), (64, 129, 16, 17), (128, 128, 13, 14), (128, 129, 8, 9)])
+def test_short_forwards_stay_whole(dim, rows, whole, split):
+    """A launch that ends within the host's part of a call is not split; items of up to 128 rows take 0.7
+    of the time."""
     def info(steps):
-        return sra.launch_info([SampleGeom(1, 2, 32, 1, 64, steps - 1)], sra.SCHED_FORWARD, heads=2, head_dim=dim)
+        g = SampleGeom(1, 1, rows, steps - (rows + 63) // 64, 8, 8)
+        return sra.launch_info([g], sra.SCHED_FORWARD, heads=2, head_dim=dim)
     assert info(whole)[2] == 0
     assert info(split)[2] > 0
