@@ -500,7 +500,8 @@ double partials_us(int64_t bytes) {
 // compute units would hold. Not for launches of over kSplitRounds rounds: there the order that keeps
 // items of a head in step on an XCD is worth more than the last round. unit_us: one unit of the
 // times in microseconds. A launch that ends before `least` stays whole.
-std::vector<int32_t> choose_split(const std::vector<Timed>& v, int64_t max_bytes, double unit_us, double least, double* end) {
+std::vector<int32_t> choose_split(const std::vector<Timed>& v, int64_t max_bytes, double unit_us, double least, bool exact,
+                                  double* end) {
   const size_t n = v.size();
   std::vector<int32_t> best(n, 1);
   *end = 0;
@@ -522,34 +523,50 @@ std::vector<int32_t> choose_split(const std::vector<Timed>& v, int64_t max_bytes
   const size_t m = at.size() - 1;
   std::vector<int32_t> chosen(m, 1), k(m, 1), last;
   std::vector<std::pair<double, int64_t>> t;
-  auto eval = [&](const std::vector<int32_t>& parts, int64_t bytes) {
+  // the launch's end, or any value over `bound` where it ends later than that
+  auto eval = [&](const std::vector<int32_t>& parts, int64_t bytes, double bound) {
     t.clear();
-    double combine = 0;
+    double combine = 0, total = 0, most = 0;
     for (size_t r = 0; r < m; ++r) {
       const Timed& x = v[at[r]];
       const KernelCost& c = *x.c;
       if (parts[r] > 1) combine = std::max(combine, c.combine);
-      t.push_back({double(x.steps) / parts[r] * c.step + c.item + (parts[r] > 1 ? c.piece : 0),
-                   int64_t(at[r + 1] - at[r]) * parts[r]});
+      const double time = double(x.steps) / parts[r] * c.step + c.item + (parts[r] > 1 ? c.piece : 0);
+      const int64_t count = int64_t(at[r + 1] - at[r]) * parts[r];
+      t.push_back({time, count});
+      most = std::max(most, time);
+      total += time * count;
     }
-    return makespan(t) + combine + partials_us(bytes) / unit_us;
+    const double more = combine + partials_us(bytes) / unit_us, least_end = std::max(most, total / kNumCus);
+    return least_end + more > bound ? least_end + more : makespan(t) + more;
   };
-  *end = eval(chosen, 0);
+  *end = eval(chosen, 0, HUGE_VAL);
   const double whole = *end;
   if (whole < least) return best;
-  for (int32_t parts = 2; parts <= 24; ++parts) {
+  // lengths of the pieces: whole parts of the longest item's; with `exact` also those at which the number
+  // of another long item's pieces changes, up to four (kinds of items then divide evenly)
+  std::vector<double> lengths;
+  for (int32_t parts = 2; parts <= 24; ++parts) lengths.push_back(longest / parts);
+  for (size_t r = 0; exact && r < m; ++r) {
+    const double x = v[at[r]].steps * v[at[r]].c->step;
+    for (int32_t parts = 1; parts <= 4 && 2 * x >= longest; ++parts)
+      if (x < parts * longest && 4 * x > parts * longest) lengths.push_back(x / parts);
+  }
+  std::sort(lengths.begin(), lengths.end(), std::greater<double>());
+  for (double length : lengths) {
     for (int tail = 0; tail < (rounds > 0 ? 2 : 1); ++tail) {
       int64_t bytes = 0;
       for (size_t r = 0; r < m; ++r) {
         const Timed& x = v[at[r]];
-        const double piece = std::max(2.0 * x.c->step, longest / parts);  // two steps at least
+        const double piece = std::max(2.0 * x.c->step, length);  // two steps at least
         k[r] = at[r] < (tail ? rounds : 0) ? 1 : std::max<int32_t>(1, int32_t(std::ceil(x.steps * x.c->step / piece - 1e-9)));
         if (k[r] > 1) bytes += k[r] * x.bytes * int64_t(at[r + 1] - at[r]);
       }
       if (bytes == 0 || bytes > max_bytes || k == last) continue;  // pieces no longer get shorter
       last = k;
-      const double e = eval(k, bytes);
-      if (e < *end && e < 0.97 * whole) {
+      const double bound = std::min((exact ? 0.98 : 1.0) * *end, 0.97 * whole);
+      const double e = eval(k, bytes, bound);
+      if (e < bound) {
         *end = e;
         chosen = k;
       }
@@ -721,7 +738,7 @@ bool best_forward_schedule(const Layout& L, int64_t max_bytes, Schedule* out) {
       if (rows <= kFwdQueryTile / 2) least /= kFwdHalfStep;
     }
     double end;
-    std::vector<int32_t> k = choose_split(timed, max_bytes, kFwdUnitUs, least, &end);
+    std::vector<int32_t> k = choose_split(timed, max_bytes, kFwdUnitUs, least, false, &end);
     if (large && !(end < 0.99 * best)) continue;
     best = end;
     total = std::accumulate(steps.begin(), steps.end(), 0.0);
@@ -810,7 +827,7 @@ void launch_backward_schedules(const Layout& L, Plan* plan) {
   std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return timed[a].time() > timed[b].time(); });
   for (int32_t i : order) sorted.push_back(timed[i]);
   double end;
-  const std::vector<int32_t> k = choose_split(sorted, kBwdPartialBytes, kBwdUnitUs, 0.0, &end);
+  const std::vector<int32_t> k = choose_split(sorted, kBwdPartialBytes, kBwdUnitUs, 0, true, &end);
   std::vector<int32_t> pk(vk.size()), pq(vq.size());
   for (size_t i = 0; i < order.size(); ++i) {
     if (size_t(order[i]) < vk.size()) pk[order[i]] = k[i];

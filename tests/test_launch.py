@@ -197,3 +197,13 @@ def test_short_forwards_stay_whole(dim, rows, whole, split):
         return sra.launch_info([g], sra.SCHED_FORWARD, heads=2, head_dim=dim)
     assert info(whole)[2] == 0
     assert info(split)[2] > 0
+
+
+def test_kinds_of_gradient_items_divide_evenly():
+    """dQ items of 26 steps, dK/dV items of 13 (gen keys) and 21: no piece length that is a whole part of
+    the longest item's cuts these into pieces of 13, 6.5 and 7, one round of the compute units."""
+    g = [SampleGeom(11, 8, 9, 11, 8, 9, group_frames=3)]
+    items, spans = sra.launch_export(g, sra.SCHED_BWD_DKDV, heads=8, head_dim=64)
+    steps = [int((-(-spans[i[4]:i[4] + i[5], 2] // 64)).sum()) for i in items]
+    assert max(steps) <= 8
+    assert len(items) + sra.launch_info(g, sra.SCHED_BWD_DQ, heads=8, head_dim=64)[0] <= 256
