@@ -8,12 +8,13 @@ still zero; only a later half (O already holding the P V of earlier halves) exer
 0 < alpha < 1. Logits with a large spread reach it: unit softmax scale on unnormalised inputs,
 where a row's max keeps rising by more than 16 log2 units as keys stream past.
 
-`mid_span_triggers` replays the kernel's key order on the host (each span's full 64-key tiles
-in span order, as two 32-key halves; lanes l and l + 32 hold the keys 8a + b and 8a + 4 + b of
-a half, b < 4; a wave is 32 query rows of a 256-row work item, rows past the item are zero) and
-counts the halves after the first whose overflow check fires with a finite m: the test asserts
-that there are many, in generation and in reference work items. Ragged span tails run a
-separate masked step and are not counted.
+`mid_span_triggers` replays the key order of what is launched (256-row items and pieces on 32x32x16
+MFMAs: each span's full 64-key tiles in span order, as two 32-key halves; lanes l and l + 32 hold
+the keys 8a + b and 8a + 4 + b of a half, b < 4; a wave is 32 query rows of a work item, rows past
+the item are zero) and counts the halves after the first whose overflow check fires with a finite m:
+the test asserts that there are many, in generation and in reference work items. Ragged span tails
+run a separate masked step and are not counted. The forward's other kernels, whose lanes hold other
+keys, are in test_gpu_forward_tiles.py.
 """
 import numpy as np
 import pytest
@@ -39,8 +40,9 @@ def mid_span_triggers(x, samples, scale, head=0):
     """(gen, ref) counts of (wave, half) events after a wave's first half where the overflow
     check fires for some row whose m is finite, with the sum above 2^17 (a margin over the
     kernel's 2^16, so fp32 against fp64 logits cannot change the count)."""
-    items, spans = sra.schedule_export(samples, sra.SCHED_FORWARD, heads=x["q_gen"].shape[1],
-                                       head_dim=x["q_gen"].shape[2])
+    heads, dim = x["q_gen"].shape[1:]
+    assert sra.launch_info(samples, sra.SCHED_FORWARD, heads=heads, head_dim=dim)[1] == 256
+    items, spans = sra.launch_export(samples, sra.SCHED_FORWARD, heads=heads, head_dim=dim)
     lanes = _lane_keys()
     q = {0: to_numpy64(x["q_gen"][:, head]), 1: to_numpy64(x["q_ref"][:, head])}
     k = {0: to_numpy64(x["k_gen"][:, head]), 1: to_numpy64(x["k_ref"][:, head])}
