@@ -97,13 +97,14 @@ def _counter_per_dispatch(path, counter):
 
 def _pmc_summary(fetch_csv, write_csv, copy_mib, workload_name, out_path):
     """Per-launch HBM bytes of each kernel: FETCH_SIZE and WRITE_SIZE (KiB per dispatch), each
-    scaled so that the copy kernel of known size reads and writes exactly its buffer."""
+    scaled so that the copy of known size reads and writes exactly its buffer (torch runs a copy
+    of 2 GiB and more as several dispatches: their sum counts)."""
     fetch = _counter_per_dispatch(fetch_csv, "FETCH_SIZE")
     write = _counter_per_dispatch(write_csv, "WRITE_SIZE")
     if "copy" not in fetch or "copy" not in write:
         raise SystemExit("the counter files hold no copy-kernel dispatch: profile a --copy-mib run")
     known_kib = copy_mib * 1024.0
-    fs, ws = known_kib / fetch["copy"][0], known_kib / write["copy"][0]
+    fs, ws = known_kib / (fetch["copy"][0] * fetch["copy"][1]), known_kib / (write["copy"][0] * write["copy"][1])
     kernels = {}
     for k in KERNEL_SYMBOLS:
         if k in fetch and k in write:

@@ -55,6 +55,18 @@ def test_traffic_summary_scales_each_counter_by_the_copy_kernel(tmp_path):
     assert set(data["kernels"]) == {"dkdv", "delta"}
 
 
+def test_a_copy_of_several_dispatches_is_one_copy(tmp_path):
+    """torch.neg over 4 GiB runs as two kernels of 2 GiB each."""
+    copy, delta = "void at::native::neg_kernel<4>()", "void sra::sra_delta_kernel<128>(sra::DeltaArgs)"
+    f, w = tmp_path / "fetch.csv", tmp_path / "write.csv"
+    _counter_csv(f, "FETCH_SIZE", [(1, copy, [1024.0]), (2, copy, [1024.0]), (3, delta, [100.0])])
+    _counter_csv(w, "WRITE_SIZE", [(1, copy, [2048.0]), (2, copy, [2048.0]), (3, delta, [10.0])])
+    bench._pmc_summary(str(f), str(w), 4, "720p", str(tmp_path / "o.json"))
+    data = json.loads((tmp_path / "o.json").read_text())
+    assert data["calibration"]["fetch_scale"] == 2.0 and data["calibration"]["write_scale"] == 1.0
+    assert data["kernels"]["delta"]["fetch_bytes"] == 200 * 1024
+
+
 def test_traffic_summary_needs_the_copy_kernel(tmp_path):
     f = tmp_path / "f.csv"
     _counter_csv(f, "FETCH_SIZE", [(2, "void sra::sra_fwd_kernel<128>(sra::FwdArgs)", [1.0])])
