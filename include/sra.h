@@ -159,7 +159,7 @@ sra_status sra_backward(const sra_problem* p,
  * device (else SRA_ERR_INVALID_ARGUMENT). A problem whose workspace (sra_workspace_size with
  * backward = 0) exceeds SRA_NOALLOC_WORKSPACE_MAX is rejected with SRA_ERR_WORKSPACE_TOO_SMALL
  * before anything is enqueued: in practice every problem whose token masks do not force the
- * compacted reference stream fits (the 720p layer needs 0.8 MB).
+ * compacted reference stream fits (the 720p layer needs 0.5 MB).
  * Allocates no device memory and no pinned host memory (no hipMalloc, hipHostMalloc or
  * hipFree): the schedule tables are copied from the plan's host image, and not at all when the
  * previous sra_forward_noalloc call on this device used the same geometry and stream (the

@@ -13,8 +13,10 @@
 // Each Q and dO fragment read from LDS feeds all four key blocks of a wave. A half's dK product
 // runs behind the next half's S product, so that it hides half of the exponentials (dP the
 // others, dV the dS). Built with MFMAs in VGPR form (S and dP live in VGPRs); the dK/dV
-// products are written as AGPR-accumulating MFMAs (mfma16_agpr). Bound by MFMA issue at the board's power
-// limit: 480p, 5 heads 7.36 ms with 32x32x16 MFMAs in 32-query tiles, 6.69 ms so.
+// products are written as AGPR-accumulating MFMAs (mfma16_agpr). Bound by the clock that the board's
+// power allows (720p: 2.20 of 2.4 GHz) and by issue: the MFMA pipes are busy 58 % of the cycles, with 1.3
+// vector instructions per MFMA; waves wait for an issue slot in 29 % of their cycles, for data in 16 %.
+// 480p, 5 heads 7.36 ms with 32x32x16 MFMAs in 32-query tiles, 6.69 ms so.
 #pragma once
 #include "sra_kernels.h"
 #include "sra_tiles.h"
