@@ -220,6 +220,11 @@ void emit_items(const TileClass& c, int tile, int32_t heads, int step,
     }
 }
 
+void longest_first(std::vector<std::pair<int64_t, WorkItem>>& v) {
+  const auto longer = [](const auto& a, const auto& b) { return a.first > b.first; };
+  if (!std::is_sorted(v.begin(), v.end(), longer)) std::stable_sort(v.begin(), v.end(), longer);
+}
+
 // Lists items in launch order. Workgroups are dealt round-robin over the 8 XCDs, so item k of
 // the launch order runs on XCD k % 8 and each XCD consumes its own subsequence in order.
 // When heads divide evenly over the XCDs, every head is pinned to one XCD (the rows it streams
@@ -233,11 +238,13 @@ void deal_items(const std::vector<WorkItem>& v, int32_t heads, Schedule* s) {
     return;
   }
   std::vector<std::vector<WorkItem>> per(kNumXcd);
+  for (auto& q : per) q.reserve(v.size() / kNumXcd + 1);
   for (const WorkItem& w : v) per[w.head % kNumXcd].push_back(w);
   size_t n = 0;
   for (auto& q : per) n = std::max(n, q.size());
   WorkItem pad{};
   pad.stream = -1;
+  s->items.reserve(n * kNumXcd);
   for (size_t j = 0; j < n; ++j)
     for (int x = 0; x < kNumXcd; ++x) s->items.push_back(j < per[x].size() ? per[x][j] : pad);
 }
@@ -251,8 +258,9 @@ void deal_items(const std::vector<WorkItem>& v, int32_t heads, Schedule* s) {
 // run back to back in step, and putting each head's short ref tiles between them staggered
 // the next head's start and nearly tripled the misses.
 void order_items(std::vector<std::pair<int64_t, WorkItem>>& v, int32_t heads, bool heads_in_turn, Schedule* s) {
-  std::stable_sort(v.begin(), v.end(), [](const auto& a, const auto& b) { return a.first > b.first; });
+  longest_first(v);
   std::vector<WorkItem> w;
+  w.reserve(v.size());
   for (auto& e : v) w.push_back(e.second);
   if (heads_in_turn && heads % kNumXcd == 0)
     std::stable_sort(w.begin(), w.end(), [](const WorkItem& a, const WorkItem& b) { return a.head < b.head; });
@@ -350,6 +358,9 @@ CostedItems query_major_items(const Layout& L, int tile, int step, Schedule* s) 
     }
   }
   CostedItems v;
+  size_t n = 0;
+  for (const TileClass& c : classes) n += size_t(L.heads) * size_t((c.rows + tile - 1) / tile);
+  v.reserve(n);
   for (const TileClass& c : classes) emit_items(c, tile, L.heads, step, s->spans, &v);
   return v;
 }
@@ -633,6 +644,8 @@ void keep_gen_queries(bool key_major, int32_t heads, Schedule* s) {
   std::vector<Span> spans;
   std::map<std::pair<int32_t, int32_t>, int32_t> made;  // (span list's offset, spans kept) -> new offset
   std::vector<int32_t> slot(size_t(s->slots) + 1, 0);   // old slot -> 1 if kept, then the new slot
+  items.reserve(s->items.size());
+  int32_t last_off = -1, last_cnt = -1, last_new = 0;  // items of one list mostly follow one another
   for (WorkItem w : s->items) {
     if (w.stream < 0) continue;
     const Span* l = &s->spans[size_t(w.span_off)];
@@ -642,9 +655,14 @@ void keep_gen_queries(bool key_major, int32_t heads, Schedule* s) {
       w.span_cnt = n;
     }
     if (key_major ? w.span_cnt == 0 : w.stream != 0) continue;
-    const auto at = made.emplace(std::make_pair(w.span_off, w.span_cnt), int32_t(spans.size()));
-    if (at.second) spans.insert(spans.end(), l, l + w.span_cnt);
-    w.span_off = at.first->second;
+    if (w.span_off != last_off || w.span_cnt != last_cnt) {
+      const auto at = made.emplace(std::make_pair(w.span_off, w.span_cnt), int32_t(spans.size()));
+      if (at.second) spans.insert(spans.end(), l, l + w.span_cnt);
+      last_off = w.span_off;
+      last_cnt = w.span_cnt;
+      last_new = at.first->second;
+    }
+    w.span_off = last_new;
     if (w.slot) slot[size_t(w.slot)] = 1;
     items.push_back(w);
   }
@@ -666,7 +684,7 @@ void keep_gen_queries(bool key_major, int32_t heads, Schedule* s) {
 
 // Sorts v longest first and returns the items' steps.
 std::vector<int32_t> sort_steps(CostedItems& v, const Schedule& s) {
-  std::stable_sort(v.begin(), v.end(), [](const auto& a, const auto& b) { return a.first > b.first; });
+  longest_first(v);
   std::map<std::pair<int32_t, int32_t>, int32_t> known;
   std::vector<int32_t> steps;
   steps.reserve(v.size());
@@ -820,6 +838,8 @@ void launch_backward_schedules(const Layout& L, Plan* plan) {
   const KernelCost &dkv_cost = kDkvCosts[L.head_dim == 128], &dq_cost = kDqCosts[L.head_dim == 128];
   const std::vector<int32_t> sk = sort_steps(vk, dkv), sq = sort_steps(vq, dq);
   std::vector<Timed> timed, sorted;
+  timed.reserve(sk.size() + sq.size());
+  sorted.reserve(sk.size() + sq.size());
   for (int32_t n : sk) timed.push_back({n, &dkv_cost, slot_bytes(kDkvKeyTile, L.head_dim, 2, 0)});
   for (int32_t n : sq) timed.push_back({n, &dq_cost, slot_bytes(kDqQueryTile, L.head_dim, 1, 0)});
   std::vector<int32_t> order(timed.size());
