@@ -116,6 +116,8 @@ sra_status sra_workspace_size(const sra_problem* p, int backward, size_t* bytes)
  * Out: o_gen bf16 [sumG, H, d], o_ref bf16 [sumR, H, d] (dense);
  *      lse_gen fp32 [H, sumG], lse_ref fp32 [H, sumR]: natural-log log-sum-exp of the scaled
  *      logits of each query row (-inf for rows of invalid frames).
+ * Results are deterministic: every sum's order is fixed by the problem. It follows the launch, and so
+ * the whole batch and all heads: a sample or head computed in another batch may differ by rounding.
  * workspace: device buffer of at least sra_workspace_size(p, 0) bytes, 256-byte aligned; its
  * contents are scratch and need no initialisation. Every output element is written. */
 sra_status sra_forward(const sra_problem* p,
