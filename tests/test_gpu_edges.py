@@ -93,3 +93,22 @@ def test_rows_masked_by_an_infinite_head_dim(heads, d, split):
     o, _, lse, _ = sra.forward(*[x[n] for n in ("q_gen", "k_gen", "v_gen", "q_ref", "k_ref", "v_ref")], [s])
     torch.cuda.synchronize()
     assert bool((lse == float("-inf")).all()) and bool(o.isnan().all())
+
+
+@pytest.mark.parametrize("heads,d,samples", [
+    (16, 64, [SampleGeom(6, 33, 54, 9, 33, 54, group_frames=18)]),  # reference items split, gen items whole
+    (16, 128, [SampleGeom(9, 40, 41, 6, 40, 41), SampleGeom(2, 20, 20, 8, 40, 40, group_frames=8)]),  # phases
+])
+def test_gen_only_calls_are_the_gen_rows_of_the_full_call(heads, d, samples):
+    """Bit for bit where heads are pinned to XCDs, too: o, LSE and, for do_ref = 0, dq."""
+    print(f"[gen only] heads {heads} d {d}", flush=True)
+    x = make_inputs(samples, heads, d, 90, device="cuda")
+    x["do_ref"].zero_()
+    ins = [x[n] for n in ("q_gen", "k_gen", "v_gen", "q_ref", "k_ref", "v_ref")]
+    full = sra.forward(*ins, samples)
+    grads = sra.backward(*ins, *full, x["do_gen"], x["do_ref"], samples)
+    ins[3] = None
+    o, _, lse, _ = sra.forward(*ins, samples, gen_queries_only=True)
+    g = sra.backward(*ins, o, None, lse, None, x["do_gen"], None, samples, gen_queries_only=True)
+    torch.cuda.synchronize()
+    assert torch.equal(o, full[0]) and torch.equal(lse, full[2]) and torch.equal(g["dq_gen"], grads["dq_gen"])
